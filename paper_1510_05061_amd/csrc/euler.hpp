@@ -88,7 +88,7 @@ template <class T>
 struct SweepConst {
   T gamma;        // ratio of specific heats
   T gm1;          // gamma - 1
-  T inv_gm1;      // 1 / (gamma - 1)
+  T enthalpy;     // gamma / (gamma - 1)
   T dtdx;         // dt / dx
   T kick;         // dt g / 2 along the sweep axis (gravity half kick)
   T dtg;          // dt g along the sweep axis
@@ -103,7 +103,7 @@ __device__ __forceinline__ SweepConst<T> make_const(double dt, double dx, double
   SweepConst<T> k;
   k.gamma = T(gamma);
   k.gm1 = T(gamma - 1.0);
-  k.inv_gm1 = T(1.0 / (gamma - 1.0));
+  k.enthalpy = T(gamma / (gamma - 1.0));
   double dtdx = dt / dx;
   k.dtdx = T(dtdx);
   k.kick = T(0.5 * dt * g);
@@ -200,7 +200,26 @@ __device__ __forceinline__ void face_states(const Prim<T>& Wl, const Prim<T>& W,
 
 // HLLC flux across the interface between the left face state L and the
 // right face state R.  Branches: S_L >= 0 -> F_L; S* >= 0 -> left star;
-// S_R > 0 -> right star; else F_R.  Only the upwind side is evaluated.
+// S_R > 0 -> right star; else F_R.  Only the upwind side K is evaluated.
+//
+// With a = rho (S_K - u), g = f - 1 = (S* - u)/(S_K - S*) and
+// f = (S_K - u)/(S_K - S*), the star correction S_K (U*_K - U_K) is
+//   rho:  S_K rho g                          =: m
+//   m_n:  S_K rho (f S* - u)                 =  m S_K
+//   m_t:  S_K rho g t                        =  m t
+//   E:    S_K (g E + f (S* - u)(rho S* + p/(S_K - u)))
+//                                            =  S_K g (E + p + a S*)
+// (f S* - u = g S_K, and f (S* - u) = g (S_K - u)), so the transverse fluxes
+// are the mass flux times t, and one reciprocal serves the whole correction.
+// Every term carries g, so a state with S* = u (a contact at rest, a mirror
+// wall) gets no correction at all, whatever the rounding of the reciprocal;
+// off the star region g S_K is set to zero instead of branching.
+// The sweeps that hold planes in LDS are bound by instruction issue: written
+// term by term (with p/(S_K - u) and two more products per variable) the
+// column march had 2962 VALU instructions instead of 2789, and a step pair
+// took 20.59 instead of 20.04 ms on a 768^3 FP32 grid (fused windows), 19.74
+// instead of 19.22 ms on 4096 FP32 patches; the HBM-bound separate sweeps
+// gain about 1 %.
 template <class T>
 __device__ __forceinline__ Cons<T> hllc(const Prim<T>& L, const Prim<T>& R,
                                         const SweepConst<T>& k) {
@@ -210,7 +229,7 @@ __device__ __forceinline__ Cons<T> hllc(const Prim<T>& L, const Prim<T>& R,
   T SR = fmax_(L.u + cL, R.u + cR);
   T aL = L.r * (SL - L.u);
   T aR = R.r * (SR - R.u);
-  T num = (R.p - L.p) + fma_(aL, L.u, -(aR * R.u));
+  T num = fma_(aL, L.u, fma_(-aR, R.u, R.p - L.p));
   T den = aL - aR;
   T Ss = div_(num, den);
   bool left = (SL >= T(0)) | (Ss >= T(0));
@@ -221,34 +240,19 @@ __device__ __forceinline__ Cons<T> hllc(const Prim<T>& L, const Prim<T>& R,
   T t2 = left ? L.t2 : R.t2;
   T p = left ? L.p : R.p;
   T S = left ? SL : SR;
+  T a = left ? aL : aR;
   T v2 = fma_(u, u, fma_(t1, t1, t2 * t2));
-  T E = fma_(p, k.inv_gm1, T(0.5) * r * v2);
+  T H = fma_(p, k.enthalpy, T(0.5) * r * v2);  // E + p
+  T sg = S * div_(Ss - u, S - Ss);
+  sg = star ? sg : T(0);
   T ru = r * u;
+  T m = r * sg;
   Cons<T> F;
-  F.r = ru;
-  F.mn = fma_(ru, u, p);
-  F.mt1 = ru * t1;
-  F.mt2 = ru * t2;
-  F.e = u * (E + p);
-  if (star) {
-    // U*_K - U_K written through g = f_K - 1 = (S* - u)/(S_K - S*), with
-    // f_K = (S_K - u)/(S_K - S*):
-    //   rho: rho g;  m_n: rho ((S* - u) + g S*);  m_t: rho t g;
-    //   E:   g E + f_K (S* - u)(rho S* + p/(S_K - u)).
-    // Every term carries S* - u or g, so a state with S* = u (a contact at
-    // rest, a mirror wall) gets no star correction at all, whatever the
-    // rounding of the reciprocals.
-    T dS = Ss - u;
-    T g = div_(dS, S - Ss);
-    T f = T(1) + g;
-    T rg = r * g;
-    T q = fma_(p, rcp(S - u), r * Ss);
-    F.r = fma_(S, rg, F.r);
-    F.mn = fma_(S, r * fma_(g, Ss, dS), F.mn);
-    F.mt1 = fma_(S, rg * t1, F.mt1);
-    F.mt2 = fma_(S, rg * t2, F.mt2);
-    F.e = fma_(S, fma_(g, E, f * dS * q), F.e);
-  }
+  F.r = ru + m;
+  F.mn = fma_(m, S, fma_(ru, u, p));
+  F.mt1 = F.r * t1;
+  F.mt2 = F.r * t2;
+  F.e = fma_(sg, fma_(a, Ss, H), u * H);
   return F;
 }
 
