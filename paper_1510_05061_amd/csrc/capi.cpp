@@ -472,6 +472,17 @@ LaunchSweep sweep_launch(const hydro_ctx* c, int axis, int do_cfl) {
   return L;
 }
 
+// Workgroups per patch of the CFL reduction: eight cells per thread of the
+// largest patch, at most kCflBlocks workgroups in all, and no fewer than four
+// per patch of a batch.  Each workgroup ends in one atomic on one address,
+// about 6 ns: on a 256^3 FP32 grid 8192 workgroups take 0.13 ms, 2048 and
+// 1024 take 0.08 ms, on a 512^3 one 1024 are 7 % faster than 2048.
+constexpr int64_t kCflBlocks = 1024;
+int cfl_chunks(int64_t cells, int64_t npatch) {
+  const int64_t want = (cells + 8 * kReduceBlock - 1) / (8 * kReduceBlock);
+  return int(std::max<int64_t>(npatch > 1 ? 4 : 1, std::min(want, kCflBlocks / npatch)));
+}
+
 LaunchReduce reduce_launch(const hydro_ctx* c) {
   LaunchReduce L{};
   L.pool = c->pool;
@@ -480,6 +491,8 @@ LaunchReduce reduce_launch(const hydro_ctx* c) {
   L.npatch = c->batch ? c->npatch : 1;
   L.chunks = c->batch ? kBatchChunks
                       : chunks_for(int64_t(c->single.n[0]) * c->single.n[1] * c->single.n[2]);
+  L.cfl_chunks = c->batch ? cfl_chunks(c->max_patch_cells, c->npatch)
+                          : cfl_chunks(int64_t(c->single.n[0]) * c->single.n[1] * c->single.n[2], 1);
   L.gamma = c->desc.gamma;
   for (int a = 0; a < 3; ++a) L.grav[a] = c->desc.grav[a];
   L.scal = c->scal;

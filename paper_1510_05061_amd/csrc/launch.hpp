@@ -76,7 +76,8 @@ struct LaunchReduce {
   const PatchDev* patches;
   PatchDev single;
   int32_t npatch;
-  int32_t chunks;
+  int32_t chunks;      // totals: workgroups (partial sums) per patch
+  int32_t cfl_chunks;  // CFL: workgroups per patch
   double gamma;
   double grav[3];
   DevScalars* scal;
