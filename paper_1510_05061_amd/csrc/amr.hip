@@ -43,6 +43,8 @@ __device__ __forceinline__ int ghost_src(int i, int n, int bclo, int bchi, bool&
   if (i >= 0 && i < n) return i;
   const int bc = i < 0 ? bclo : bchi;
   if (bc == kBcPeriodic) {
+    const int w = i < 0 ? i + n : i - n;
+    if (w >= 0 && w < n) return w;  // at most one period away: no division
     const int m = i % n;
     return m < 0 ? m + n : m;
   }
@@ -77,10 +79,10 @@ struct AmrArgs {
   const AmrLink* dlinks;
 };
 
-// Link blockIdx.y of a launch.
+// Link l of a launch.
 template <class T>
-__device__ __forceinline__ AmrLink link_of(const AmrArgs<T>& a) {
-  return a.dlinks ? a.dlinks[blockIdx.y] : a.links[blockIdx.y];
+__device__ __forceinline__ AmrLink link_of(const AmrArgs<T>& a, int l) {
+  return a.dlinks ? a.dlinks[l] : a.links[l];
 }
 
 // Fine patch of a link: the table entry, or the patch inside a ghost-free
@@ -116,39 +118,79 @@ __device__ __forceinline__ int t1_of(int axis) { return axis == 0 ? 1 : 0; }
 __device__ __forceinline__ int t2_of(int axis) { return axis == 2 ? 1 : 2; }
 
 // Every stored ghost cell of the grid (y = 0) or of patch blockIdx.y, from
-// the interior.
+// the interior, in the order of memory: the slabs below the interior along z;
+// per interior slab its rows below along y, the g cells at either end of
+// each interior row, and its rows above; the slabs above.  Only ghost cells
+// are visited, one per thread and trip (five independent loads, then five
+// stores) at 32-bit offsets from the stored corner.
+//
+// What bounds the fill are the row ends: runs of g cells, often in lines of
+// their own, where memory writes a part of a 64-byte sector at the cost of
+// reading it first (a strided write of 16 or 32 bytes takes 2.3 times one of
+// 64).  The stores go past the caches: nothing here reads them again.
+// 1024 64^3 and 1024 32^3 patches, against a walk over every stored cell
+// with plain stores and 64-bit offsets: 4 FP32 layers, rows back to back
+// 3.44 -> 2.07 ms, padded to 128-byte lines 5.1 -> 5.2 ms (4.7 to 5.4 with
+// where the pool lies); FP64, padded, 5.8 -> 5.7 ms.
 template <class T>
 __global__ void __launch_bounds__(kAmrBlock) fill_ghosts_kernel(AmrArgs<T> a) {
   const PatchDev P = a.patches ? a.patches[blockIdx.y] : a.single;
   const int g = a.patches ? P.ng : a.ng;
   const int nx = P.n[0], ny = P.n[1], nz = P.n[2];
-  const unsigned sx = unsigned(nx + 2 * g), sxy = sx * unsigned(ny + 2 * g);
-  const unsigned total = sxy * unsigned(nz + 2 * g);  // a stored patch holds < 2^32 cells
-  T* p0 = a.pool + P.base0;
+  const unsigned g2 = 2u * unsigned(g), sx = unsigned(nx) + g2, sy = unsigned(ny) + g2;
+  const unsigned below = unsigned(g) * sy * sx;        // cells of g whole slabs
+  const unsigned edge = unsigned(g) * sx, ends = unsigned(ny) * g2;
+  const unsigned slab = 2u * edge + ends;              // ghost cells of an interior slab
+  const unsigned total = 2u * below + unsigned(nz) * slab;  // a stored patch holds < 2^32 cells
+  T* p0 = a.pool + P.base0 - int64_t(g) * (1 + int64_t(P.sy) + int64_t(P.sz));
   for (unsigned c = blockIdx.x * kAmrBlock + threadIdx.x; c < total;
        c += gridDim.x * kAmrBlock) {
-    const unsigned kk = c / sxy, rem = c - kk * sxy;
-    const unsigned jj = rem / sx;
-    const int k = int(kk) - g, j = int(jj) - g, i = int(rem - jj * sx) - g;
-    if (i >= 0 && i < nx && j >= 0 && j < ny && k >= 0 && k < nz) continue;
+    int i, j, k;
+    const unsigned m = c - below;
+    if (c < below || m >= unsigned(nz) * slab) {
+      const unsigned e = c < below ? c : m - unsigned(nz) * slab;
+      const unsigned row = e / sx, kk = row / sy;
+      i = int(e - row * sx) - g;
+      j = int(row - kk * sy) - g;
+      k = c < below ? int(kk) - g : nz + int(kk);
+    } else {
+      const unsigned kk = m / slab, r = m - kk * slab;
+      k = int(kk);
+      if (r < edge || r >= edge + ends) {
+        const unsigned e = r < edge ? r : r - edge - ends;
+        const unsigned row = e / sx;
+        i = int(e - row * sx) - g;
+        j = r < edge ? int(row) - g : ny + int(row);
+      } else {
+        const unsigned row = (r - edge) / g2, q = r - edge - row * g2;
+        i = int(q) < g ? int(q) - g : nx + int(q) - g;
+        j = int(row);
+      }
+    }
     bool fx = false, fy = false, fz = false;
     const int si = ghost_src(i, nx, a.bc[0], a.bc[1], fx);
     const int sj = ghost_src(j, ny, a.bc[2], a.bc[3], fy);
     const int sk = ghost_src(k, nz, a.bc[4], a.bc[5], fz);
-    const int64_t src = int64_t(si) + int64_t(sj) * P.sy + int64_t(sk) * P.sz;
-    const int64_t dst = int64_t(i) + int64_t(j) * P.sy + int64_t(k) * P.sz;
-    p0[dst] = p0[src];
-    p0[dst + P.plane] = fx ? -p0[src + P.plane] : p0[src + P.plane];
-    p0[dst + 2 * P.plane] = fy ? -p0[src + 2 * P.plane] : p0[src + 2 * P.plane];
-    p0[dst + 3 * P.plane] = fz ? -p0[src + 3 * P.plane] : p0[src + 3 * P.plane];
-    p0[dst + 4 * P.plane] = p0[src + 4 * P.plane];
+    // a plane is below 4 GiB: element offsets from its corner fit 32 bits
+    const unsigned src = unsigned(si + g) + unsigned(sj + g) * unsigned(P.sy) +
+                         unsigned(sk + g) * unsigned(P.sz);
+    const unsigned dst = unsigned(i + g) + unsigned(j + g) * unsigned(P.sy) +
+                         unsigned(k + g) * unsigned(P.sz);
+    T v[5];
+#pragma unroll
+    for (int w = 0; w < 5; ++w) v[w] = (p0 + w * P.plane)[src];
+    if (fx) v[1] = -v[1];
+    if (fy) v[2] = -v[2];
+    if (fz) v[3] = -v[3];
+#pragma unroll
+    for (int w = 0; w < 5; ++w) __builtin_nontemporal_store(v[w], p0 + w * P.plane + dst);
   }
 }
 
 // Coarse cells covered by the fine patch of link blockIdx.y.
 template <class T>
 __global__ void __launch_bounds__(kAmrBlock) restrict_kernel(AmrArgs<T> a) {
-  const AmrLink L = link_of(a);
+  const AmrLink L = link_of(a, int(blockIdx.y));
   const PatchDev F = fine_patch(a.fpatches, L.fine, a.finset), C = a.patches[L.coarse];
   const unsigned cx = unsigned(F.n[0] / 2), cxy = cx * unsigned(F.n[1] / 2);
   const unsigned total = cxy * unsigned(F.n[2] / 2);
@@ -191,111 +233,178 @@ __device__ __forceinline__ double mc_slope(double a, double b) {
   return same ? copysign(m, a) : 0.0;
 }
 
-// Fine cells (interior, or the stored ghost shell) of link blockIdx.y, one
-// coarse parent per thread: the parent's value and its three limited slopes
-// are formed once and give each of its children that is written.  SHELL (a
-// thin ghost shell): only the parents with a ghost child, and variable
-// blockIdx.z per thread; else the whole box of parents, all five variables
-// per thread (their loads issued together).
-template <class T, bool COLD, bool SHELL>
-__global__ void __launch_bounds__(kAmrBlock) prolong_kernel(AmrArgs<T> a) {
-  const AmrLink L = link_of(a);
-  const PatchDev F = fine_patch(a.fpatches, L.fine, a.finset), C = a.patches[L.coarse];
-  const int nx = F.n[0], ny = F.n[1], nz = F.n[2];
+// Two x-neighbours at p (element pair; PAIR: aligned to it, one access).
+template <class T>
+struct alignas(2 * sizeof(T)) Pair {
+  T a, b;
+};
+template <bool PAIR, class T>
+__device__ __forceinline__ void store_pair(T* p, T a, T b) {
+  if (PAIR) {
+    *reinterpret_cast<Pair<T>*>(p) = Pair<T>{a, b};
+  } else {
+    p[0] = a;
+    p[1] = b;
+  }
+}
+
+// Whether the x pairs (2i, 2i + 1) of a patch start on pairs of elements in
+// every row and plane (the pool is 16-byte aligned).
+__device__ __forceinline__ bool pairs_aligned(const PatchDev& F) {
+  return ((F.base0 | F.plane | F.sy | F.sz) & 1) == 0;
+}
+
+// Link and workgroup of a link launch: with a grid of (bx, n) workgroups,
+// dispatched round robin over the eight XCDs, the workgroups of one link are
+// given to one XCD, whose L2 then holds the coarse lines they share (the
+// level step on 338 patches 2.97 -> 2.86 ms).  Workgroups past the last
+// multiple of eight links keep their place.
+__device__ __forceinline__ void link_block(int& link, unsigned& bx) {
+  const unsigned G = gridDim.x, n8 = gridDim.y & ~7u, b = blockIdx.y * G + blockIdx.x;
+  if (b < n8 * G) {
+    const unsigned r = b >> 3, q = r / G;
+    link = int(q * 8 + (b & 7));
+    bx = r - q * G;
+  } else {
+    link = int(blockIdx.y);
+    bx = blockIdx.x;
+  }
+}
+
+// Fine cells (interior, or the stored ghost shell) of a link, one coarse
+// parent per thread: per variable the parent's value and its three limited
+// slopes are formed once and give its children, written as x pairs (PAIR:
+// one access each).  Fine extents are even, so a parent's children are all
+// inside or all outside the interior, and only with an odd number of ghost
+// layers (ODD) can some of them lie beyond the stored shell.
+//
+// The interior's parents are a box.  The shell's are walked as three parts:
+// whole planes of parents below and above the interior's along z; within its
+// z range whole rows below and above it along y; within both the parents
+// below and above it along x (rows of ceil(g/2) + ceil(g/2)).
+//
+// The interior is bound by instruction issue (FP64 slopes in the definition's
+// order), the shell by its x ends (parts of 64-byte sectors, as the ghost
+// fill).  Against one test and one 64-bit offset per child over the whole box
+// of parents (2047 instructions a thread, now about 850): 128 FP32 links of
+// 32^3 cells, interior 51 -> 31 us, 4 ghost layers 137 -> 104 us; the level
+// step's 338 shells of 4 layers 209 -> 167 us, interpolated 272 -> 245 us.
+template <class T, bool COLD, bool PAIR, bool ODD>
+__device__ void prolong_link(const AmrArgs<T>& a, const AmrLink& L, const PatchDev& F,
+                             const PatchDev& C, unsigned bx) {
   const int g = a.ghosts_only ? F.ng : 0;
-  // parents of the fine cells -g .. n + g - 1 along each axis
-  const int lo = (-g) >> 1;
-  const unsigned px = unsigned(((nx + g - 1) >> 1) - lo + 1);
-  const unsigned py = unsigned(((ny + g - 1) >> 1) - lo + 1);
-  const unsigned pz = unsigned(((nz + g - 1) >> 1) - lo + 1);
-  const unsigned pxy = px * py;
-  // ghosts only: the parents outside the block of parents [0, (n + 1) / 2)
-  // along some axis (the others have every child in the interior), as three
-  // parts: whole planes below and above the block along z; within the
-  // block's z range, whole rows below and above it along y; within both,
-  // the cells below and above it along x
-  const unsigned ix = unsigned((nx + 1) >> 1), iy = unsigned((ny + 1) >> 1),
-                 iz = unsigned((nz + 1) >> 1);
-  const unsigned oz = pz - iz, oy = py - iy, ox = px - ix;
-  const unsigned nz_part = oz * pxy, ny_part = iz * oy * px;
-  const unsigned total = SHELL ? pxy * pz - ix * iy * iz : pxy * pz;
-  // t-th parent outside the block [0, I) along an axis: lo .. -1, then I ..
+  const int h = (g + 1) >> 1;  // parents beyond the interior's on each side
+  const unsigned ix = unsigned(F.n[0]) >> 1, iy = unsigned(F.n[1]) >> 1,
+                 iz = unsigned(F.n[2]) >> 1;  // the interior's parents
+  const unsigned o = 2u * unsigned(h), px = ix + o, py = iy + o;
+  const unsigned zpart = o * py * px, ypart = iz * o * px;
+  const unsigned total = g ? zpart + ypart + iz * iy * o : iz * iy * ix;
+  // t-th parent outside [0, I) along an axis: -h .. -1, then I ..
   auto outside = [&](unsigned t, unsigned I) {
-    return int(t) < -lo ? lo + int(t) : int(I) + int(t) + lo;
+    return int(t) < h ? int(t) - h : int(I) + int(t) - h;
   };
-  T* f0 = a.fpool + F.base0;
-  const T* c0 = a.pool + C.base0;
-  const T* o0 = COLD ? a.cold + C.base0 : nullptr;
+  // wave-uniform bases and one 32-bit byte offset per cell (a plane is below
+  // 4 GiB): the coarse base is the lowest neighbour of the lowest parent, the
+  // fine base its first child
+  const int64_t corner = C.base0 + (L.ox - h - 1) + int64_t(L.oy - h - 1) * C.sy +
+                         int64_t(L.oz - h - 1) * C.sz;
+  const T* c0 = a.pool + corner;
+  const T* o0 = COLD ? a.cold + corner : nullptr;
+  T* f0 = a.fpool + F.base0 - 2 * h * (1 + int64_t(F.sy) + int64_t(F.sz));
+  const unsigned csy = unsigned(C.sy) * sizeof(T), csz = unsigned(C.sz) * sizeof(T);
+  const unsigned fsy = unsigned(F.sy) * sizeof(T), fsz = unsigned(F.sz) * sizeof(T);
+  auto at = [](const T* p, unsigned b) {
+    return reinterpret_cast<const T*>(reinterpret_cast<const char*>(p) + b);
+  };
   const double th = a.theta;
-  if (blockIdx.x * kAmrBlock >= total) return;
-  for (unsigned c = blockIdx.x * kAmrBlock + threadIdx.x; c < total;
-       c += gridDim.x * kAmrBlock) {
+  for (unsigned c = bx * kAmrBlock + threadIdx.x; c < total; c += gridDim.x * kAmrBlock) {
     int pi, pj, pk;
-    if (!SHELL) {
-      const unsigned kk = c / pxy, rem = c - kk * pxy;
-      const unsigned jj = rem / px;
-      pk = int(kk) + lo;
-      pj = int(jj) + lo;
-      pi = int(rem - jj * px) + lo;
-      // a parent whose children are all interior has none in the ghost shell
-      if (a.ghosts_only && pi >= 0 && 2 * pi < nx && pj >= 0 && 2 * pj < ny && pk >= 0 &&
-          2 * pk < nz)
-        continue;
-    } else if (c < nz_part) {
-      const unsigned kk = c / pxy, rem = c - kk * pxy;
-      const unsigned jj = rem / px;
+    if (!g) {
+      const unsigned row = c / ix, kk = row / iy;
+      pi = int(c - row * ix);
+      pj = int(row - kk * iy);
+      pk = int(kk);
+    } else if (c < zpart) {
+      const unsigned row = c / px, kk = row / py;
+      pi = int(c - row * px) - h;
+      pj = int(row - kk * py) - h;
       pk = outside(kk, iz);
-      pj = int(jj) + lo;
-      pi = int(rem - jj * px) + lo;
-    } else if (c < nz_part + ny_part) {
-      const unsigned d = c - nz_part, row = oy * px;
-      const unsigned kk = d / row, rem = d - kk * row;
-      const unsigned jj = rem / px;
+    } else if (c < zpart + ypart) {
+      const unsigned d = c - zpart, row = d / px, kk = row / o;
+      pi = int(d - row * px) - h;
+      pj = outside(row - kk * o, iy);
       pk = int(kk);
-      pj = outside(jj, iy);
-      pi = int(rem - jj * px) + lo;
     } else {
-      const unsigned d = c - nz_part - ny_part, row = iy * ox;
-      const unsigned kk = d / row, rem = d - kk * row;
-      const unsigned jj = rem / ox;
+      const unsigned d = c - zpart - ypart, row = d / o, kk = row / iy;
+      pi = outside(d - row * o, ix);
+      pj = int(row - kk * iy);
       pk = int(kk);
-      pj = int(jj);
-      pi = outside(rem - jj * ox, ix);
     }
-    const int64_t pc = int64_t(L.ox + pi) + int64_t(L.oy + pj) * C.sy +
-                       int64_t(L.oz + pk) * C.sz;
-    const int v0 = SHELL ? int(blockIdx.z) : 0;
+    const unsigned pc = unsigned(pi + h + 1) * unsigned(sizeof(T)) + unsigned(pj + h + 1) * csy +
+                        unsigned(pk + h + 1) * csz;
+    const unsigned fc = 2 * (unsigned(pi + h) * unsigned(sizeof(T)) + unsigned(pj + h) * fsy +
+                             unsigned(pk + h) * fsz);
+    double u[5][7];
 #pragma unroll
-    for (int v = v0; v < (SHELL ? v0 + 1 : 5); ++v) {
-      const T* q = c0 + pc + v * C.plane;
-      const T* qo = COLD ? o0 + pc + v * C.plane : nullptr;
-      // coarse value at offset d, interpolated in time when a start copy is given
-      auto cv = [&](int64_t d) {
+    for (int v = 0; v < 5; ++v) {
+      const T* q = c0 + v * C.plane;
+      const T* qo = COLD ? o0 + v * C.plane : nullptr;
+      // coarse value at byte offset b, interpolated in time when a start copy is given
+      auto cv = [&](unsigned b) {
         if constexpr (!COLD) {
-          return double(q[d]);
+          return double(*at(q, b));
         } else {
-          const double o = double(qo[d]);
-          return o + th * (double(q[d]) - o);
+          const double w = double(*at(qo, b));
+          return w + th * (double(*at(q, b)) - w);
         }
       };
-      const double u = cv(0);
-      const double dx = mc_slope(u - cv(-1), cv(1) - u);
-      const double dy = mc_slope(u - cv(-C.sy), cv(C.sy) - u);
-      const double dz = mc_slope(u - cv(-C.sz), cv(C.sz) - u);
-      T* fv = f0 + v * F.plane;
+      u[v][0] = cv(pc);
+      u[v][1] = cv(pc - unsigned(sizeof(T)));
+      u[v][2] = cv(pc + unsigned(sizeof(T)));
+      u[v][3] = cv(pc - csy);
+      u[v][4] = cv(pc + csy);
+      u[v][5] = cv(pc - csz);
+      u[v][6] = cv(pc + csz);
+    }
 #pragma unroll
-      for (int ch = 0; ch < 8; ++ch) {
-        const int i = 2 * pi + (ch & 1), j = 2 * pj + ((ch >> 1) & 1), k = 2 * pk + (ch >> 2);
-        if (i < -g || i >= nx + g || j < -g || j >= ny + g || k < -g || k >= nz + g) continue;
-        const bool inside = i >= 0 && i < nx && j >= 0 && j < ny && k >= 0 && k < nz;
-        if (inside == bool(a.ghosts_only)) continue;
-        const double ox = (ch & 1) ? 0.25 : -0.25, oy = ((ch >> 1) & 1) ? 0.25 : -0.25,
-                     oz = (ch >> 2) ? 0.25 : -0.25;
-        fv[int64_t(i) + int64_t(j) * F.sy + int64_t(k) * F.sz] =
-            T(((u + ox * dx) + oy * dy) + oz * dz);
+    for (int v = 0; v < 5; ++v) {
+      const double w = u[v][0];
+      const double dx = mc_slope(w - u[v][1], u[v][2] - w);
+      const double dy = mc_slope(w - u[v][3], u[v][4] - w);
+      const double dz = mc_slope(w - u[v][5], u[v][6] - w);
+      T* fv = f0 + v * F.plane;
+      const double x0 = w + -0.25 * dx, x1 = w + 0.25 * dx;
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        const double oy = (r & 1) ? 0.25 : -0.25, oz = (r >> 1) ? 0.25 : -0.25;
+        const T y0 = T((x0 + oy * dy) + oz * dz), y1 = T((x1 + oy * dy) + oz * dz);
+        T* f = const_cast<T*>(at(fv, fc + (r & 1) * fsy + (r >> 1) * fsz));
+        if (!ODD) {
+          store_pair<PAIR>(f, y0, y1);
+        } else {
+          const int i = 2 * pi, j = 2 * pj + (r & 1), k = 2 * pk + (r >> 1);
+          if (j < -g || j >= F.n[1] + g || k < -g || k >= F.n[2] + g) continue;
+          if (i >= -g) f[0] = y0;
+          if (i + 1 < F.n[0] + g) f[1] = y1;
+        }
       }
     }
   }
+}
+
+template <class T, bool COLD>
+__global__ void __launch_bounds__(kAmrBlock) prolong_kernel(AmrArgs<T> a) {
+  int l;
+  unsigned bx;
+  link_block(l, bx);
+  const AmrLink L = link_of(a, l);
+  const PatchDev F = fine_patch(a.fpatches, L.fine, a.finset), C = a.patches[L.coarse];
+  if (a.ghosts_only && (F.ng & 1))
+    prolong_link<T, COLD, false, true>(a, L, F, C, bx);
+  else if (pairs_aligned(F))
+    prolong_link<T, COLD, true, false>(a, L, F, C, bx);
+  else
+    prolong_link<T, COLD, false, false>(a, L, F, C, bx);
 }
 
 // Copy of the coarse cells within a.margin of the box link blockIdx.y
@@ -304,7 +413,7 @@ __global__ void __launch_bounds__(kAmrBlock) prolong_kernel(AmrArgs<T> a) {
 // same values.
 template <class T>
 __global__ void __launch_bounds__(kAmrBlock) snapshot_kernel(AmrArgs<T> a) {
-  const AmrLink L = link_of(a);
+  const AmrLink L = link_of(a, int(blockIdx.y));
   const PatchDev F = fine_patch(a.fpatches, L.fine, a.finset), C = a.patches[L.coarse];
   const int m = a.margin;
   const unsigned bx = unsigned(F.n[0] / 2 + 2 * m), bxy = bx * unsigned(F.n[1] / 2 + 2 * m);
@@ -368,7 +477,7 @@ __device__ __forceinline__ void face_flux(const T* p0, const PatchDev& P, int ax
 // a.weight, added to the register.
 template <class T>
 __global__ void __launch_bounds__(kAmrBlock) flux_reg_kernel(AmrArgs<T> a) {
-  const AmrLink L = link_of(a);
+  const AmrLink L = link_of(a, int(blockIdx.y));
   const int side = int(blockIdx.z);
   const PatchDev F = fine_patch(a.fpatches, L.fine, a.finset);
   const int axis = a.axis, a1 = t1_of(axis), a2 = t2_of(axis);
@@ -487,7 +596,7 @@ static_assert(kAmrBlock % 16 == 0, "whole lane groups per workgroup");
 // Refluxing of link blockIdx.y across its a.side faces along a.axis.
 template <class T>
 __global__ void __launch_bounds__(kAmrBlock) reflux_kernel(AmrArgs<T> a) {
-  const AmrLink L = link_of(a);
+  const AmrLink L = link_of(a, int(blockIdx.y));
   const PatchDev F = fine_patch(a.fpatches, L.fine, a.finset);
   const PatchDev C = a.patches[L.coarse];
   const int axis = a.axis, a1 = t1_of(axis), a2 = t2_of(axis), side = a.side;
@@ -585,27 +694,19 @@ template <class T>
 static hipError_t launch_amr_t(const LaunchAmr& L, hipStream_t st) {
   const AmrArgs<T> a = to_aargs<T>(L);
   if (L.op == kAmrFill) {
-    // a batch: a few workgroups per patch striding over its stored cells
+    // four ghost cells per thread of the patch with the most
     const unsigned ny = L.patches ? unsigned(L.npatch) : 1u;
-    const unsigned nx = L.patches ? std::min(amr_blocks(L.cells), 32u) : amr_blocks(L.cells);
+    const unsigned nx = amr_blocks((L.cells + 3) / 4);
     hipLaunchKernelGGL(fill_ghosts_kernel<T>, dim3(nx, ny), dim3(kAmrBlock), 0, st, a);
   } else if (L.op == kAmrRestrict) {
     hipLaunchKernelGGL(restrict_kernel<T>, dim3(amr_blocks(L.cells), unsigned(L.nlinks)),
                        dim3(kAmrBlock), 0, st, a);
   } else if (L.op == kAmrProlong) {
-    const dim3 grid(amr_blocks(L.cells), unsigned(L.nlinks), L.shell ? 5u : 1u);
-    if (L.shell && !L.ghosts_only) return hipErrorInvalidValue;
-    if (L.cold) {
-      if (L.shell)
-        hipLaunchKernelGGL((prolong_kernel<T, true, true>), grid, dim3(kAmrBlock), 0, st, a);
-      else
-        hipLaunchKernelGGL((prolong_kernel<T, true, false>), grid, dim3(kAmrBlock), 0, st, a);
-    } else {
-      if (L.shell)
-        hipLaunchKernelGGL((prolong_kernel<T, false, true>), grid, dim3(kAmrBlock), 0, st, a);
-      else
-        hipLaunchKernelGGL((prolong_kernel<T, false, false>), grid, dim3(kAmrBlock), 0, st, a);
-    }
+    const dim3 grid(amr_blocks(L.cells), unsigned(L.nlinks));
+    if (L.cold)
+      hipLaunchKernelGGL((prolong_kernel<T, true>), grid, dim3(kAmrBlock), 0, st, a);
+    else
+      hipLaunchKernelGGL((prolong_kernel<T, false>), grid, dim3(kAmrBlock), 0, st, a);
   } else if (L.op == kAmrSnapshot) {
     hipLaunchKernelGGL(snapshot_kernel<T>, dim3(amr_blocks(L.cells), unsigned(L.nlinks)),
                        dim3(kAmrBlock), 0, st, a);
