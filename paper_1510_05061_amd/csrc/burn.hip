@@ -21,8 +21,8 @@
 // plane size, pitches and interior origin).
 #include <hip/hip_runtime.h>
 
-#include <algorithm>
-
+#include "euler.hpp"
+#include "fastdiv.hpp"
 #include "launch.hpp"
 
 namespace hydro {
@@ -37,72 +37,120 @@ struct BurnArgs {
   double gamma;
   double h;
   int nsub;
+  unsigned cells;
+  FastDiv dnx, dny;  // division by nx and ny
   double A[kBurnMaxSpecies - 1];
   double Ta[kBurnMaxSpecies - 1];
   double B[kBurnMaxSpecies];
 };
 
+// One wavefront pass of J substeps over the chain: at time t substep j
+// updates species t - j, so J independent chains are in flight.  Each update
+// reads the same values as in sequential order (substep j's species s-1 is
+// written at time t-1, and substep j+1 overwrites it only after substep j,
+// later in the same time step), so the bits are those of the plain loop.
+template <int M, int J, class First, class Next>
+__device__ __forceinline__ void substeps(First first, Next next) {
+#pragma unroll
+  for (int t = 0; t < M + J - 1; ++t) {
+#pragma unroll
+    for (int j = 0; j < J; ++j) {
+      const int s = t - j;
+      if (s == 0) first();
+      else if (s > 0 && s < M) next(s);
+    }
+  }
+}
+template <int M, class First, class Next>
+__device__ __forceinline__ void all_substeps(int nsub, First first, Next next) {
+  int n = 0;
+  for (; n + 4 <= nsub; n += 4) substeps<M, 4>(first, next);
+  for (; n < nsub; ++n) substeps<M, 1>(first, next);
+}
+
+// From kScaledSubsteps substeps on, the chain is stepped in scaled species
+// W_s = X_s / a_s with a_s = e_1 .. e_s, e_s = c_s d_s: the update
+// X_s <- d_s X_s + e_s X_{s-1} becomes W_s <- d_s W_s + W_{s-1}, one FMA (and
+// one rounding) per species and substep instead of two.  The scaling costs
+// about 14 instructions per species, two an update are saved: it pays from
+// seven substeps on.  A zone whose a_s leave [2^-400, 2^64] (a frozen link;
+// the bounds keep W within range and X / a_s from underflow) is stepped as
+// it stands.
+constexpr int kScaledSubsteps = 8;
+
+// The kernel is bound by FP64 issue.  13 species and 64 substeps on 256^3
+// FP32 zones: with (X_s + c_s X_{s-1}) d_s as three operations, a division
+// per link for Ta / T and the network's constants hoisted out of a
+// grid-stride loop into spilled scalars 1.72 ms; now 0.98 ms (held to 128 registers it spills: 1.32 ms).
 template <class T, int M>
 __global__ void __launch_bounds__(kBurnBlock) burn_kernel(BurnArgs<T> a) {
   const PatchDev& P = a.single;
-  const unsigned nx = unsigned(P.n[0]), ny = unsigned(P.n[1]);
-  const unsigned cells = nx * ny * unsigned(P.n[2]);
-  T* p0 = a.pool + P.base0;
-  T* x0 = a.X + P.base0;
-  for (unsigned i = blockIdx.x * kBurnBlock + threadIdx.x; i < cells;
-       i += gridDim.x * kBurnBlock) {
-    const unsigned row = i / nx, x = i - row * nx;
-    const unsigned z = row / ny, y = row - z * ny;
-    const int64_t o = int64_t(x) + int64_t(y) * P.sy + int64_t(z) * P.sz;
-    const double r = double(p0[o]);
-    const double mx = double(p0[o + P.plane]), my = double(p0[o + 2 * P.plane]);
-    const double mz = double(p0[o + 3 * P.plane]), e = double(p0[o + 4 * P.plane]);
-    const double m2 = mx * mx + my * my + mz * mz;
-    const double temp = ((a.gamma - 1.0) * (e - (0.5 * m2) / r)) / r;
-    double X[M], c[M], d[M];
-    double e0 = 0.0;
+  const unsigned i = blockIdx.x * kBurnBlock + threadIdx.x;
+  if (i >= a.cells) return;
+  const unsigned row = a.dnx.div(i), x = i - row * a.dnx.d;
+  const unsigned z = a.dny.div(row), y = row - z * a.dny.d;
+  const int64_t o = int64_t(x) + int64_t(y) * P.sy + int64_t(z) * P.sz;
+  T* p0 = a.pool + P.base0 + o;
+  T* x0 = a.X + P.base0 + o;
+  const double r = double(p0[0]);
+  const double mx = double(p0[P.plane]), my = double(p0[2 * P.plane]);
+  const double mz = double(p0[3 * P.plane]), e = double(p0[4 * P.plane]);
+  double X[M], c[M], d[M];
 #pragma unroll
-    for (int s = 0; s < M; ++s) {
-      X[s] = double(x0[o + s * P.plane]);
-      e0 += a.B[s] * X[s];
-    }
+  for (int s = 0; s < M; ++s) X[s] = double(x0[s * P.plane]);
+  const double m2 = mx * mx + my * my + mz * mz;
+  const double temp = ((a.gamma - 1.0) * (e - (0.5 * m2) / r)) / r;
+  // Ta / T for every link from one reciprocal: the residual of the product
+  // corrects it to the quotient (a rounding error of the exponent would be
+  // carried through all substeps); at T = 0 the product is the quotient
+  const double itemp = 1.0 / temp;
+  const bool finite = fabs(itemp) < __builtin_huge_val();
+  auto over_temp = [&](double ta) {
+    const double q = ta * itemp;
+    return finite ? fma(fma(-q, temp, ta), itemp, q) : q;
+  };
+  double e0 = 0.0;
 #pragma unroll
-    for (int s = 0; s < M; ++s) {
-      const double k = s < M - 1 ? a.A[s] * exp(-a.Ta[s] / temp) : 0.0;
-      d[s] = 1.0 / (1.0 + a.h * k);
-      if (s + 1 < M) c[s + 1] = a.h * k;
-    }
-    // Substeps four at a time as a wavefront: at time t substep j updates
-    // species t - j.  Each update reads the same values as in sequential
-    // order (substep j's species s-1 is written at time t-1, and substep
-    // j+1 overwrites it only after substep j, later in the same time step),
-    // so the bits are those of the plain loop, with four independent
-    // dependency chains in flight instead of one.
-    int n = 0;
-    for (; n + 4 <= a.nsub; n += 4) {
+  for (int s = 0; s < M; ++s) e0 += a.B[s] * X[s];
+  c[0] = 0.0;
 #pragma unroll
-      for (int t = 0; t < M + 3; ++t) {
-#pragma unroll
-        for (int j = 0; j < 4; ++j) {
-          const int s = t - j;
-          if (s == 0) X[0] *= d[0];
-          else if (s > 0 && s < M) X[s] = (X[s] + c[s] * X[s - 1]) * d[s];
-        }
-      }
-    }
-    for (; n < a.nsub; ++n) {
-      X[0] *= d[0];
-#pragma unroll
-      for (int s = 1; s < M; ++s) X[s] = (X[s] + c[s] * X[s - 1]) * d[s];
-    }
-    double e1 = 0.0;
-#pragma unroll
-    for (int s = 0; s < M; ++s) {
-      e1 += a.B[s] * X[s];
-      x0[o + s * P.plane] = T(X[s]);
-    }
-    p0[o + 4 * P.plane] = T(e + r * (e1 - e0));
+  for (int s = 0; s < M; ++s) {
+    const double hk = s < M - 1 ? a.h * (a.A[s] * exp(-over_temp(a.Ta[s]))) : 0.0;
+    d[s] = s < M - 1 ? 1.0 / (1.0 + hk) : 1.0;
+    if (s + 1 < M) c[s + 1] = hk;
   }
+  bool scaled = a.nsub >= kScaledSubsteps;
+  if (scaled) {
+    double g = 1.0;
+#pragma unroll
+    for (int s = 1; s < M; ++s) {
+      g *= c[s] * d[s];
+      scaled = scaled && g >= 0x1p-400 && g <= 0x1p64;
+    }
+  }
+  if (scaled) {
+    double g = 1.0;
+#pragma unroll
+    for (int s = 1; s < M; ++s) {
+      g *= c[s] * d[s];
+      c[s] = g;  // a_s
+      X[s] *= rcp(g);
+    }
+    all_substeps<M>(a.nsub, [&] { X[0] *= d[0]; },
+                    [&](int s) { X[s] = s < M - 1 ? fma(d[s], X[s], X[s - 1]) : X[s] + X[s - 1]; });
+#pragma unroll
+    for (int s = 1; s < M; ++s) X[s] *= c[s];
+  } else {
+    all_substeps<M>(a.nsub, [&] { X[0] *= d[0]; },
+                    [&](int s) { X[s] = fma(c[s], X[s - 1], X[s]) * d[s]; });
+  }
+  double e1 = 0.0;
+#pragma unroll
+  for (int s = 0; s < M; ++s) {
+    e1 += a.B[s] * X[s];
+    x0[s * P.plane] = T(X[s]);
+  }
+  p0[4 * P.plane] = T(e + r * (e1 - e0));
 }
 
 template <class T, int M>
@@ -131,9 +179,11 @@ static hipError_t launch_burn_t(const LaunchBurn& L, hipStream_t st) {
     a.Ta[i] = L.Ta[i];
   }
   for (int s = 0; s < L.nspec; ++s) a.B[s] = L.B[s];
-  const int64_t cells = int64_t(L.single.n[0]) * L.single.n[1] * L.single.n[2];
-  const int64_t b = (cells + kBurnBlock - 1) / kBurnBlock;
-  const dim3 grid(unsigned(std::max<int64_t>(1, std::min<int64_t>(b, 65536))));
+  // a plane is below 4 GiB: the cells and the workgroups fit 32 bits
+  a.cells = unsigned(L.single.n[0]) * unsigned(L.single.n[1]) * unsigned(L.single.n[2]);
+  a.dnx = FastDiv(uint32_t(L.single.n[0]));
+  a.dny = FastDiv(uint32_t(L.single.n[1]));
+  const dim3 grid((a.cells + kBurnBlock - 1) / kBurnBlock);
   return launch_burn_m<T, 2>(L, a, grid, st);
 }
 
