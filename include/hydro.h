@@ -78,7 +78,8 @@ typedef enum hydro_bc {
 typedef enum hydro_precision { HYDRO_FP32 = 0, HYDRO_FP64 = 1 } hydro_precision;
 
 /* hydro_desc.flags */
-#define HYDRO_FLAG_NO_GRAPH 0x1u /* launch kernels one by one, no hipGraph */
+#define HYDRO_FLAG_NO_GRAPH 0x1u /* accepted and without effect: steps are
+                                    always launched kernel by kernel */
 #define HYDRO_FLAG_NO_TUNE 0x2u  /* skip the autotuner and its cache; use the
                                     built-in default configuration */
 #define HYDRO_BATCH_PER_PATCH_DT 0x4u /* batches: every patch keeps its own
@@ -167,9 +168,9 @@ int hydro_workspace_bytes(const hydro_desc* d, size_t* bytes);
  * least hydro_workspace_bytes bytes (16-byte aligned), `stream` a
  * hipStream_t (NULL: the null stream).  Validates the
  * descriptor, picks the kernel configuration (autotuner cache, or a timing
- * search with dt = 0, which leaves the state bit for bit), captures the
- * even- and odd-step graphs, sets t = 0 and step = 0.  Synchronous.
- * On success *out owns only host objects and hipGraphExecs; free it with
+ * search with dt = 0, which leaves the state bit for bit), plans the
+ * launches of even and odd steps, sets t = 0 and step = 0.  Synchronous.
+ * On success *out owns only host objects; free it with
  * hydro_destroy.  Errors: HYDRO_EINVAL, HYDRO_EDEVICE. */
 int hydro_init(const hydro_desc* d, void* state, size_t state_bytes, void* workspace,
                size_t ws_bytes, void* stream, hydro_ctx** out);
@@ -514,7 +515,9 @@ int hydro_clear_error(hydro_ctx* c);
  *                          per workgroup; m=1 selects the chunked march (one
  *                          pencil per wave), G caps its grid (0: none);
  *                          without m the lane-run sweep;
- *   y:q=Q,s=S  z:q=Q,s=S   column marches: Q columns per tile, S segments;
+ *   y:q=Q,s=S  z:q=Q,s=S   column marches: Q columns per tile, S segments (Q a
+ *                          multiple of 64, or 16 or 32 on a single grid of at
+ *                          most 1024 such tiles);
  *   p:g=G,d=D,f=F          batch: G persistent workgroups, D = 1 ticket or
  *                          0 round-robin work items, F = 1 fuses the x and
  *                          y sweeps per patch z-plane;
@@ -523,7 +526,7 @@ int hydro_clear_error(hydro_ctx* c);
  * hydro_get_config writes at most len bytes including the NUL.
  * hydro_set_config replaces it (validated: HYDRO_EINVAL for a shape the
  * kernels do not support, e.g. f=1 when a patch plane exceeds 80 KiB; work
- * lists are rebuilt and graphs re-captured).  Every valid configuration
+ * lists and launches are rebuilt).  Every valid configuration
  * gives the same bits. */
 int hydro_get_config(hydro_ctx* c, char* buf, size_t len);
 int hydro_set_config(hydro_ctx* c, const char* cfg);

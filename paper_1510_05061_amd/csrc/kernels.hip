@@ -51,6 +51,7 @@ struct SweepArgs {
   double* tpart;             // totals partials (null: no totals)
   double gvec[3];            // gravity vector (totals: phi = -g . x)
   int32_t tonly;             // totals of the current state: dt = 0, no stores
+  int32_t tail;              // direct launches with totals: kTailNone, kTailSum or kTailStep
   const double* pdt;         // persistent: dt per patch (null: scal->dt)
   unsigned long long* psmax; // persistent: CFL maximum per patch
   T* dst;                    // out-of-place result (null: pool, in place)
@@ -176,10 +177,43 @@ __device__ __forceinline__ void inv_widths(const PatchDev& P, T id[3]) {
   for (int a = 0; a < 3; ++a) id[a] = T(P.idx[a]);  // 1/dx, made on the host
 }
 
+// v of every lane moved by the DPP pattern CTRL (one row of 16 lanes; every
+// source lane lies in the destination's row), as two 32-bit moves.
+template <int CTRL>
+__device__ __forceinline__ double dpp_f64(double v) {
+  const unsigned long long b = (unsigned long long)__double_as_longlong(v);
+  const unsigned lo = unsigned(__builtin_amdgcn_update_dpp(0, int(unsigned(b)), CTRL, 0xF, 0xF, false));
+  const unsigned hi = unsigned(__builtin_amdgcn_update_dpp(0, int(unsigned(b >> 32)), CTRL, 0xF, 0xF, false));
+  return __longlong_as_double((long long)(((unsigned long long)hi << 32) | lo));
+}
+
+__device__ __forceinline__ double lane_f64(double v, int lane) {
+  const unsigned long long b = (unsigned long long)__double_as_longlong(v);
+  const unsigned lo = unsigned(__builtin_amdgcn_readlane(int(unsigned(b)), lane));
+  const unsigned hi = unsigned(__builtin_amdgcn_readlane(int(unsigned(b >> 32)), lane));
+  return __longlong_as_double((long long)(((unsigned long long)hi << 32) | lo));
+}
+template <int CTRL>
+__device__ __forceinline__ double dpp_mov(double v) { return dpp_f64<CTRL>(v); }
+template <int CTRL>
+__device__ __forceinline__ float dpp_mov(float v) {
+  return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), CTRL, 0xF, 0xF, false));
+}
+__device__ __forceinline__ float lane_of(float v, int lane) {
+  return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), lane));
+}
+__device__ __forceinline__ double lane_of(double v, int lane) { return lane_f64(v, lane); }
+
+// Max over the 64 lanes of a full wave: register moves within the rows of 16
+// lanes, then the four row maxima (as wave_sum below; six LDS permutes of
+// about 100 cycles each before).
 template <class T>
 __device__ __forceinline__ T wave_max(T v) {
-  for (int off = 32; off > 0; off >>= 1) v = fmax_(v, __shfl_xor(v, off));
-  return v;
+  v = fmax_(v, dpp_mov<0xB1>(v));   // quad_perm [1,0,3,2]
+  v = fmax_(v, dpp_mov<0x4E>(v));   // quad_perm [2,3,0,1]
+  v = fmax_(v, dpp_mov<0x141>(v));  // row_half_mirror
+  v = fmax_(v, dpp_mov<0x140>(v));  // row_mirror
+  return fmax_(fmax_(lane_of(v, 0), lane_of(v, 16)), fmax_(lane_of(v, 32), lane_of(v, 48)));
 }
 
 // Workgroup max of smax folded into the FP64 atomic at `dst` (the bit
@@ -304,23 +338,6 @@ __device__ __forceinline__ void tot_add(Acc& t, const Cons<T>& S, const PatchDev
   }
 }
 
-// v of every lane moved by the DPP pattern CTRL (one row of 16 lanes; every
-// source lane lies in the destination's row), as two 32-bit moves.
-template <int CTRL>
-__device__ __forceinline__ double dpp_f64(double v) {
-  const unsigned long long b = (unsigned long long)__double_as_longlong(v);
-  const unsigned lo = unsigned(__builtin_amdgcn_update_dpp(0, int(unsigned(b)), CTRL, 0xF, 0xF, false));
-  const unsigned hi = unsigned(__builtin_amdgcn_update_dpp(0, int(unsigned(b >> 32)), CTRL, 0xF, 0xF, false));
-  return __longlong_as_double((long long)(((unsigned long long)hi << 32) | lo));
-}
-
-__device__ __forceinline__ double lane_f64(double v, int lane) {
-  const unsigned long long b = (unsigned long long)__double_as_longlong(v);
-  const unsigned lo = unsigned(__builtin_amdgcn_readlane(int(unsigned(b)), lane));
-  const unsigned hi = unsigned(__builtin_amdgcn_readlane(int(unsigned(b >> 32)), lane));
-  return __longlong_as_double((long long)(((unsigned long long)hi << 32) | lo));
-}
-
 // Sum over the 64 lanes of a full wave, in a fixed tree: within each row of
 // 16 lanes by register moves across lanes (pairs, quads, halves of a row,
 // rows: each step adds a lane and its mirror, so every lane of a row ends
@@ -351,10 +368,57 @@ __device__ void tot_block(Acc& t, double vol, double* out, double* red, bool gra
   if (threadIdx.x < 6) {
     double a = red[threadIdx.x];
     for (int w = 1; w < nw; ++w) a += red[w * 6 + threadIdx.x];
-    out[threadIdx.x] = a;
+    // device scope: step_tail reads it from another workgroup
+    __hip_atomic_store(&out[threadIdx.x], a, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   }
   __syncthreads();
   t.zero();
+}
+
+__device__ void next_dt(DevScalars* s);
+
+// The end of a step inside its last sweep (direct launches of few
+// workgroups): the last workgroup to finish sums the partials of all of them
+// in a fixed order (threads in strides of the workgroup, then lanes, then
+// waves) and, for kTailStep, ends the step as totals_finish_kernel does.
+// Every thread calls this after tot_block and the CFL fold, whose stores and
+// atomics wave 0 made at device scope; they are complete (vmcnt) before it
+// counts the workgroup, and the partials are read at device scope.
+template <class T>
+__device__ void step_tail(const SweepArgs<T>& a, double* red) {
+  if (a.tail == kTailNone) return;
+  __shared__ int last;
+  DevScalars* s = a.scal;
+  if (threadIdx.x == 0) {
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    last = atomicAdd(&s->tdone, 1u) == gridDim.x - 1;
+  }
+  __syncthreads();
+  if (!last) return;
+  double acc[6] = {0, 0, 0, 0, 0, 0};
+  for (unsigned i = threadIdx.x; i < gridDim.x; i += blockDim.x)
+#pragma unroll
+    for (int v = 0; v < 6; ++v)
+      acc[v] += __hip_atomic_load(&a.tpart[6 * i + v], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  const int nw = (blockDim.x + 63) >> 6;
+#pragma unroll
+  for (int v = 0; v < 6; ++v) {
+    const double w = wave_sum(acc[v]);
+    if ((threadIdx.x & 63) == 0) red[(threadIdx.x >> 6) * 6 + v] = w;
+  }
+  __syncthreads();
+  if (threadIdx.x < 6) {
+    double t = red[threadIdx.x];
+    for (int w = 1; w < nw; ++w) t += red[w * 6 + threadIdx.x];
+    s->totals[threadIdx.x] = t;
+  }
+  if (threadIdx.x == 0) {
+    s->tdone = 0u;
+    if (a.tail == kTailStep) {
+      s->t += s->dt;
+      next_dt(s);
+    }
+  }
 }
 
 // LDS bytes per thread that tot_block_wide needs
@@ -792,6 +856,7 @@ __global__ void __launch_bounds__(512, sizeof(T) == 4 && TOT && !MULTI && !PERSI
     }
   }
   finish_block(a.scal, smax, bad, a.do_cfl != 0 && !a.pdt, red);
+  if constexpr (TOT && !PERSIST) step_tail(a, tred);
 }
 
 // --------------------------------------------------------------------------
@@ -1141,6 +1206,7 @@ __global__ void __launch_bounds__(512, sizeof(T) == 4 && !PERSIST ? 3 : 1)
     }
   }
   finish_block(a.scal, smax, bad, a.do_cfl != 0 && !a.pdt, red);
+  if constexpr (TOT && !PERSIST) step_tail(a, tred);
 }
 
 // --------------------------------------------------------------------------
@@ -1882,6 +1948,7 @@ __global__ void __launch_bounds__(512, sizeof(T) == 4 ? (PERSIST && TOT ? 3 : kC
     }
   }
   finish_block(a.scal, smax, bad, a.do_cfl != 0 && !a.pdt, red);
+  if constexpr (TOT && !PERSIST) step_tail(a, tred);
 }
 
 // --------------------------------------------------------------------------
@@ -2009,10 +2076,11 @@ __global__ void __launch_bounds__(256) totals_final_kernel(const double* partial
 // --------------------------------------------------------------------------
 
 __device__ void next_dt(DevScalars* s) {
-  double smax = __longlong_as_double((long long)s->smax_bits);
+  double smax = __longlong_as_double((long long)__hip_atomic_load(
+      &s->smax_bits, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
   double dt = s->cfl / smax;
   if (!(smax > 0.0) || !(smax < __builtin_huge_val())) {
-    s->error |= kErrSpeed;
+    atomicOr(&s->error, kErrSpeed);
     dt = 0.0;
   }
   if (s->t_end > 0.0) dt = fmin(dt, fmax(0.0, s->t_end - s->t));
@@ -2157,6 +2225,7 @@ static SweepArgs<T> to_args(const LaunchSweep& L) {
   for (int i = 0; i < 3; ++i) a.gvec[i] = L.gvec[i];
   a.tonly = L.totals_only;
   a.pdt = L.pdt;
+  a.tail = L.tail;
   a.psmax = L.psmax;
   a.dst = static_cast<T*>(L.dst);
   a.wins = L.wins;

@@ -17,6 +17,11 @@ constexpr int kWinXY = 3;      // fused x then y sweeps of single-grid windows
 constexpr int kWinYX = 4;      // fused y then x sweeps of single-grid windows
 constexpr int kZPlane = 5;     // z sweep of patch x-z planes in LDS (batches)
 
+// What the last workgroup of a direct launch with totals does once every
+// partial is written: nothing, sum them into the totals, or also end the step
+// (t += dt, next dt).
+constexpr int kTailNone = 0, kTailSum = 1, kTailStep = 2;
+
 struct LaunchSweep {
   // pool: state or patch pool; patches/items: device tables (persistent)
   void* pool;
@@ -45,6 +50,7 @@ struct LaunchSweep {
   // at tpart + 6 * index; null: none
   double* tpart;
   double gvec[3];            // gravity vector (totals: phi = -g . x)
+  int32_t tail;              // what the last workgroup of the launch does (below)
   int32_t totals_only;       // dt = 0 and nothing stored: totals of the current state
   int32_t tot_cap;           // direct x launches with totals: at most this many
                              // workgroups, striding over the tiles (0: no cap)
