@@ -67,7 +67,7 @@ __device__ __forceinline__ void count_bin(C* ctr, int b) {
   for (int k = 0; k < 2; ++k) {
     const unsigned long long m = __ballot(todo);
     if (m == 0ull) return;  // wave-uniform
-    const int lead = __shfl(b, int(__builtin_ctzll(m)));
+    const int lead = __builtin_amdgcn_readlane(b, int(__builtin_ctzll(m)));
     const bool mine = todo && b == lead;
     const unsigned long long same = __ballot(mine);
     if (mine) {
@@ -105,14 +105,21 @@ struct DiagArgs {
 // patch blockIdx.y: workgroups stride over the flattened cells (x fastest,
 // coalesced), count into LDS, then add their nonzero counters to the global
 // 64-bit counters (exact: integer adds commute).
-template <class T, int Q>
-__global__ void __launch_bounds__(kDiagBlock) pdf_kernel(DiagArgs<T> a) {
+//
+// A workgroup ends by adding its counters to the global ones: with 1000 bins
+// and 4096 workgroups on 256^3 cells that was half the time (100 us for the
+// density, 57 us so).  Up to 8192 counters take workgroups of 256 threads;
+// up to kPdfLdsBins, where one or two workgroups fill the LDS of a CU,
+// workgroups of 1024.  Counting straight into memory instead took 11.2 ms
+// for 20000 bins (0.10 ms so) and is left for more.
+template <class T, int Q, int BLOCK>
+__global__ void __launch_bounds__(BLOCK) pdf_kernel(DiagArgs<T> a) {
   extern __shared__ unsigned int hist[];
   const bool batch = a.patches != nullptr;
   const PatchDev P = batch ? a.patches[blockIdx.y] : a.single;
   const int nb2 = a.nbins + 2;
   if (a.lds) {
-    for (int i = threadIdx.x; i < nb2; i += kDiagBlock) hist[i] = 0u;
+    for (int i = threadIdx.x; i < nb2; i += BLOCK) hist[i] = 0u;
     __syncthreads();
   }
   const unsigned nx = unsigned(P.n[0]), ny = unsigned(P.n[1]);
@@ -120,13 +127,13 @@ __global__ void __launch_bounds__(kDiagBlock) pdf_kernel(DiagArgs<T> a) {
   const FastDiv dnx = batch ? FastDiv(nx) : a.dnx, dny = batch ? FastDiv(ny) : a.dny;
   const T* p0 = a.pool + P.base0;
   constexpr int U = kDiagCells;
-  const unsigned stride = gridDim.x * kDiagBlock * U;
-  for (unsigned i0 = blockIdx.x * kDiagBlock * U + threadIdx.x; i0 < cells; i0 += stride) {
+  const unsigned stride = gridDim.x * BLOCK * U;
+  for (unsigned i0 = blockIdx.x * BLOCK * U + threadIdx.x; i0 < cells; i0 += stride) {
     // the U cells' offsets, then their quantities (all loads issued first)
     int64_t o[U];
 #pragma unroll
     for (int u = 0; u < U; ++u) {
-      const unsigned i = min(i0 + unsigned(u) * kDiagBlock, cells - 1);
+      const unsigned i = min(i0 + unsigned(u) * BLOCK, cells - 1);
       const unsigned row = dnx.div(i), x = i - row * nx;
       const unsigned z = dny.div(row), y = row - z * ny;
       o[u] = int64_t(x) + int64_t(y) * P.sy + int64_t(z) * P.sz;
@@ -136,7 +143,7 @@ __global__ void __launch_bounds__(kDiagBlock) pdf_kernel(DiagArgs<T> a) {
     for (int u = 0; u < U; ++u) q[u] = diag_quantity<T, Q>(p0, P.plane, o[u], a.gamma);
 #pragma unroll
     for (int u = 0; u < U; ++u) {
-      const bool valid = i0 + unsigned(u) * kDiagBlock < cells;
+      const bool valid = i0 + unsigned(u) * BLOCK < cells;
       const int b = valid ? diag_bin(q[u], a.lo, a.w, a.nbins) : -1;
       if (a.lds)
         count_bin(hist, b);
@@ -146,7 +153,7 @@ __global__ void __launch_bounds__(kDiagBlock) pdf_kernel(DiagArgs<T> a) {
   }
   if (a.lds) {
     __syncthreads();
-    for (int i = threadIdx.x; i < nb2; i += kDiagBlock)
+    for (int i = threadIdx.x; i < nb2; i += BLOCK)
       if (hist[i]) atomicAdd(&a.counts[i], (unsigned long long)hist[i]);
   }
 }
@@ -218,72 +225,104 @@ __global__ void __launch_bounds__(kDiagBlock) profile_slab_kernel(DiagArgs<T> a)
   }
 }
 
-// Slabs normal to x (axis 0): thread x of workgroup (c, xb) sums rows
-// c, c + C, ... (U of them in flight) of the grid at its own x into
-// partials[x][c][5].
+// Slabs normal to x (axis 0): a workgroup (c, xb) of 1024 threads holds R
+// rows of w = min(nx, 256) neighbouring x each; thread (x, r) sums the rows
+// c R + r, (c + C) R + r, ... (U of them in flight) at its own x, then the
+// threads of an x add their sums in the order of r into partials[x][c][5].
+// One row per workgroup of 256 threads left a quarter of the waves: 155
+// against 116 us on 256^3 FP32.
+constexpr int kXslabBlock = 1024;
+constexpr int kXslabWidth = 256;
+__host__ __device__ inline int xslab_width(int nx) { return nx < kXslabWidth ? nx : kXslabWidth; }
+__host__ __device__ inline int xslab_rows(int nx) { return kXslabBlock / xslab_width(nx); }
 template <class T>
-__global__ void __launch_bounds__(kDiagBlock) profile_xslab_kernel(DiagArgs<T> a) {
+__global__ void __launch_bounds__(kXslabBlock) profile_xslab_kernel(DiagArgs<T> a) {
+  __shared__ double red[5][kXslabBlock];
   const PatchDev& P = a.single;
-  const int c = blockIdx.x;
-  const int x = blockIdx.y * kDiagBlock + threadIdx.x;
-  if (x >= P.n[0]) return;
+  const int c = blockIdx.x, w = xslab_width(P.n[0]), R = xslab_rows(P.n[0]);
+  const int rg = threadIdx.x / w, xi = threadIdx.x - rg * w, x = blockIdx.y * w + xi;
   const unsigned ny = unsigned(P.n[1]), rows = ny * unsigned(P.n[2]);
   const T* p0 = a.pool + P.base0;
   constexpr int U = kDiagCells;
-  const unsigned C = unsigned(a.chunks);
+  const unsigned C = unsigned(a.chunks) * R;
   double acc[5] = {0.0, 0.0, 0.0, 0.0, 0.0};
-  for (unsigned r0 = unsigned(c); r0 < rows; r0 += C * U) {
-    double cv[U][5];
+  if (rg < R && x < P.n[0]) {
+    for (unsigned r0 = unsigned(c * R + rg); r0 < rows; r0 += C * U) {
+      double cv[U][5];
 #pragma unroll
-    for (int u = 0; u < U; ++u) {
-      const unsigned r = min(r0 + unsigned(u) * C, rows - 1);
-      const unsigned z = a.dny.div(r), y = r - z * ny;
-      load_cell<T>(p0, P.plane, int64_t(x) + int64_t(y) * P.sy + int64_t(z) * P.sz, cv[u]);
+      for (int u = 0; u < U; ++u) {
+        const unsigned r = min(r0 + unsigned(u) * C, rows - 1);
+        const unsigned z = a.dny.div(r), y = r - z * ny;
+        load_cell<T>(p0, P.plane, int64_t(x) + int64_t(y) * P.sy + int64_t(z) * P.sz, cv[u]);
+      }
+#pragma unroll
+      for (int u = 0; u < U; ++u)
+        if (r0 + unsigned(u) * C < rows) profile_add<T>(cv[u], a, acc);
     }
-#pragma unroll
-    for (int u = 0; u < U; ++u)
-      if (r0 + unsigned(u) * C < rows) profile_add<T>(cv[u], a, acc);
   }
-  for (int v = 0; v < 5; ++v) a.partials[(int64_t(x) * a.chunks + c) * 5 + v] = acc[v];
+#pragma unroll
+  for (int v = 0; v < 5; ++v) red[v][threadIdx.x] = acc[v];
+  __syncthreads();
+  // sum i = (x, v) of the tile
+  for (int i = threadIdx.x; i < 5 * w; i += kXslabBlock) {
+    const int xo = i / 5, v = i - 5 * xo, xg = blockIdx.y * w + xo;
+    if (xg >= P.n[0]) continue;
+    double t = red[v][xo];
+    for (int q = 1; q < R; ++q) t += red[v][q * w + xo];
+    a.partials[(int64_t(xg) * a.chunks + c) * 5 + v] = t;
+  }
 }
 
 // Sum of v over the workgroup in a fixed order (wave shuffles, then the
 // waves in order); the result is returned to every thread.
+template <int BLOCK = kDiagBlock>
 __device__ __forceinline__ double block_sum(double v, double* red) {
   for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off);
   __syncthreads();  // red is free
   if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = v;
   __syncthreads();
   double t = red[0];
-  for (int w = 1; w < kDiagBlock / 64; ++w) t += red[w];
+  for (int w = 1; w < BLOCK / 64; ++w) t += red[w];
   return t;
 }
 
-// Slab means out[s][v] = sum_c partials[s][c][v] / cells per slab (thread t
-// takes slabs t, t + 256, ...), then the mixing width and mixedness from
-// per-thread sums reduced in a fixed order (one workgroup).
-__global__ void __launch_bounds__(kDiagBlock) profile_final_kernel(const double* partials,
+// Slab means out[s][v] = sum_c partials[s][c][v] / cells per slab, then the
+// mixing width and mixedness from per-thread sums over slabs t, t + 1024, ...
+// reduced in a fixed order (one workgroup: 15 us with a thread per slab and
+// one partial at a time, 3 us so; 256 slabs of 16 partials).
+constexpr int kFinalBlock = 1024;
+__global__ void __launch_bounds__(kFinalBlock) profile_final_kernel(const double* partials,
                                                                      int nslab, int chunks,
                                                                      double cells_per_slab,
                                                                      double dx_axis, double* out) {
-  __shared__ double red[kDiagBlock / 64];
+  __shared__ double red[kFinalBlock / 64];
   double w = 0.0, num = 0.0, den = 0.0;
-  for (int s = threadIdx.x; s < nslab; s += kDiagBlock) {
-    double m[5];
+  // the means: a thread per slab and field, eight partials in flight
+  for (int i = threadIdx.x; i < 5 * nslab; i += kFinalBlock) {
+    const int s = i / 5, v = i - 5 * s;
+    const double* p = partials + int64_t(s) * chunks * 5 + v;
+    double t = 0.0;
+    int c = 0;
+    for (; c + 8 <= chunks; c += 8) {
+      double x[8];
 #pragma unroll
-    for (int v = 0; v < 5; ++v) {
-      double t = 0.0;
-      for (int c = 0; c < chunks; ++c) t += partials[(int64_t(s) * chunks + c) * 5 + v];
-      m[v] = t / cells_per_slab;
-      out[s * 5 + v] = m[v];
+      for (int q = 0; q < 8; ++q) x[q] = p[(c + q) * 5];
+#pragma unroll
+      for (int q = 0; q < 8; ++q) t += x[q];
     }
-    w += 4.0 * m[3] * (1.0 - m[3]);
-    den += m[3] * (1.0 - m[3]);
-    num += m[4];
+    for (; c < chunks; ++c) t += p[c * 5];
+    out[i] = t / cells_per_slab;
   }
-  w = block_sum(w, red);
-  den = block_sum(den, red);
-  num = block_sum(num, red);
+  __syncthreads();  // the means are visible to the workgroup
+  for (int s = threadIdx.x; s < nslab; s += kFinalBlock) {
+    const double f = out[s * 5 + 3];
+    w += 4.0 * f * (1.0 - f);
+    den += f * (1.0 - f);
+    num += out[s * 5 + 4];
+  }
+  w = block_sum<kFinalBlock>(w, red);
+  den = block_sum<kFinalBlock>(den, red);
+  num = block_sum<kFinalBlock>(num, red);
   if (threadIdx.x == 0) {
     out[nslab * 5] = w * dx_axis;
     out[nslab * 5 + 1] = den > 0.0 ? num / den : 0.0;
@@ -457,19 +496,31 @@ static hipError_t launch_pdf_t(const LaunchDiag& L, hipStream_t st) {
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
   const size_t lds = a.lds ? size_t(nb2) * sizeof(unsigned int) : 0;
+  const bool wide = a.lds && nb2 > kPdfNarrowBins;
   dim3 grid;
   if (L.patches) {
-    grid = dim3(kPdfPatchBlocks, unsigned(L.npatch));
+    grid = dim3(wide ? 1 : kPdfPatchBlocks, unsigned(L.npatch));
   } else {
+    // at least 8192 cells and 12 cells per counter to a workgroup (256^3
+    // cells: 16 bins 64 -> 45 us with half the workgroups of 4096 cells,
+    // 1000 bins 100 -> 55 us), one workgroup per CU of wide counters
     const int64_t cells = int64_t(L.single.n[0]) * L.single.n[1] * L.single.n[2];
-    const int64_t b = (cells + 4 * kDiagBlock - 1) / (4 * kDiagBlock);
-    grid = dim3(unsigned(std::max<int64_t>(1, std::min<int64_t>(b, kPdfMaxBlocks))));
+    int64_t b = wide ? kPdfWideBlocks : std::min<int64_t>(cells / (12 * nb2), kPdfMaxBlocks);
+    b = std::max<int64_t>(std::min<int64_t>(b, cells / 8192), kPdfWideBlocks);
+    b = std::min<int64_t>(b, (cells + 4 * kDiagBlock - 1) / (4 * kDiagBlock));
+    grid = dim3(unsigned(std::max<int64_t>(1, a.lds ? b : kPdfMaxBlocks)));
   }
+  auto run = [&](auto narrow_kernel, auto wide_kernel) {
+    if (wide)
+      hipLaunchKernelGGL(wide_kernel, grid, dim3(1024), lds, st, a);
+    else
+      hipLaunchKernelGGL(narrow_kernel, grid, dim3(kDiagBlock), lds, st, a);
+  };
   switch (L.quantity) {
-    case kQRho: hipLaunchKernelGGL((pdf_kernel<T, kQRho>), grid, dim3(kDiagBlock), lds, st, a); break;
-    case kQPressure: hipLaunchKernelGGL((pdf_kernel<T, kQPressure>), grid, dim3(kDiagBlock), lds, st, a); break;
-    case kQSpeed: hipLaunchKernelGGL((pdf_kernel<T, kQSpeed>), grid, dim3(kDiagBlock), lds, st, a); break;
-    case kQMach: hipLaunchKernelGGL((pdf_kernel<T, kQMach>), grid, dim3(kDiagBlock), lds, st, a); break;
+    case kQRho: run(pdf_kernel<T, kQRho, kDiagBlock>, pdf_kernel<T, kQRho, 1024>); break;
+    case kQPressure: run(pdf_kernel<T, kQPressure, kDiagBlock>, pdf_kernel<T, kQPressure, 1024>); break;
+    case kQSpeed: run(pdf_kernel<T, kQSpeed, kDiagBlock>, pdf_kernel<T, kQSpeed, 1024>); break;
+    case kQMach: run(pdf_kernel<T, kQMach, kDiagBlock>, pdf_kernel<T, kQMach, 1024>); break;
     default: return hipErrorInvalidValue;
   }
   return hipGetLastError();
@@ -486,15 +537,15 @@ static hipError_t launch_profile_t(const LaunchDiag& L, hipStream_t st) {
   const int ns = L.single.n[L.axis];
   if (L.axis == 0)
     hipLaunchKernelGGL(profile_xslab_kernel<T>,
-                       dim3(unsigned(L.chunks), unsigned((ns + kDiagBlock - 1) / kDiagBlock)),
-                       dim3(kDiagBlock), 0, st, a);
+                       dim3(unsigned(L.chunks), unsigned((ns + xslab_width(ns) - 1) / xslab_width(ns))),
+                       dim3(kXslabBlock), 0, st, a);
   else
     hipLaunchKernelGGL(profile_slab_kernel<T>, dim3(unsigned(L.chunks), unsigned(ns)),
                        dim3(kDiagBlock), 0, st, a);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
   const double cells = double(L.single.n[0]) * L.single.n[1] * L.single.n[2];
-  hipLaunchKernelGGL(profile_final_kernel, dim3(1), dim3(kDiagBlock), 0, st, L.partials, ns,
+  hipLaunchKernelGGL(profile_final_kernel, dim3(1), dim3(kFinalBlock), 0, st, L.partials, ns,
                      L.chunks, cells / ns, L.dx_axis, L.out);
   return hipGetLastError();
 }
@@ -507,20 +558,28 @@ static hipError_t launch_spectrum_t(const LaunchDiag& L, hipStream_t st) {
   // x-lines per pass: 8 (an FP64 state: 4, for its prefetch registers) for
   // lines of up to 256 cells, else 2 (3P/2 n <= kSpecElems)
   constexpr int PS = sizeof(T) == 8 ? 4 : 8;
+  // workgroups: about 16 passes each (a workgroup forms the twiddles and ends
+  // in a partial spectrum), 512 to kSpecBlocks of them (L.chunks): 256^3 FP32
+  // 229 -> 197 us against always kSpecBlocks, 64^3 21 -> 16 us; with 512 on
+  // 512^3, 5 % slower
+  const int64_t groups = (int64_t(L.single.n[1]) * L.single.n[2] + (sp.n <= 256 ? PS : 2) - 1) /
+                         (sp.n <= 256 ? PS : 2);
+  const int blocks = int(std::min<int64_t>(std::min<int64_t>(groups, L.chunks),
+                                           std::max<int64_t>(512, groups / 16)));
   if (sp.n <= 256) {
     const size_t lds = size_t(sp.n + fft_lds(3 * PS / 2 * sp.n)) * sizeof(double2);
-    hipLaunchKernelGGL((spectrum_kernel<T, PS>), dim3(unsigned(L.chunks)), dim3(kSpecBlock), lds,
+    hipLaunchKernelGGL((spectrum_kernel<T, PS>), dim3(unsigned(blocks)), dim3(kSpecBlock), lds,
                        st, a, sp);
   } else {
     const size_t lds = size_t(sp.n + fft_lds(3 * sp.n)) * sizeof(double2);
-    hipLaunchKernelGGL((spectrum_kernel<T, 2>), dim3(unsigned(L.chunks)), dim3(kSpecBlock), lds,
+    hipLaunchKernelGGL((spectrum_kernel<T, 2>), dim3(unsigned(blocks)), dim3(kSpecBlock), lds,
                        st, a, sp);
   }
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
   const double lines = double(L.single.n[1]) * L.single.n[2];
   hipLaunchKernelGGL(spectrum_final_kernel, dim3(unsigned(sp.n / 2 + 1)), dim3(kDiagBlock), 0,
-                     st, L.partials, L.chunks, sp.n, lines, L.out);
+                     st, L.partials, blocks, sp.n, lines, L.out);
   return hipGetLastError();
 }
 

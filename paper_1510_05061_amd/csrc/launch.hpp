@@ -95,7 +95,9 @@ struct LaunchReduce {
 
 // In-situ diagnostics (diag.hip).
 constexpr int kQRho = 0, kQPressure = 1, kQSpeed = 2, kQMach = 3;  // hydro_quantity
-constexpr int kPdfLdsBins = 8192;       // counters (bins + 2) kept in LDS up to this
+constexpr int kPdfNarrowBins = 8192;    // counters (bins + 2) of a 256-thread workgroup
+constexpr int kPdfLdsBins = 40000;      // counters kept in LDS up to this
+constexpr int kPdfWideBlocks = 256;     // workgroups of wide counters
 constexpr int kPdfMaxBins = 1 << 24;
 constexpr int kPdfMaxBlocks = 4096;     // single grid
 constexpr int kPdfPatchBlocks = 4;      // batch: workgroups per patch

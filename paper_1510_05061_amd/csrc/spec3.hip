@@ -14,9 +14,9 @@
 //      in LDS, unpacked into the three half spectra kx = 0 .. nx/2 (real
 //      input: the other half is their conjugate); written as three planes
 //      U_c[z][y][kx] of complex values.
-//   y  tiles of 4 neighbouring kx columns of one (c, z): FFT along y in LDS,
-//      written back in place.
-//   z  tiles of 4 kx columns of one ky: FFT along z of each component in
+//   y  tiles of 8 (long lines: 4) neighbouring kx columns of one (c, z): FFT
+//      along y in LDS, written back in place.
+//   z  tiles of 8 or 4 kx columns of one ky: FFT along z of each component in
 //      turn, the power summed over the components in registers, then
 //      P[ky][kz][kx] = w(kx) sum_c |U_c|^2 with w = 2 for the kx whose
 //      conjugate partner -kx is not stored (0 < kx < nx/2), else 1.
@@ -40,9 +40,15 @@ namespace hydro {
 
 constexpr int kS3Block = 256;
 constexpr int kS3Elems = 4096;  // complex elements of the x pass's lines in LDS
-constexpr int kS3T = 4;         // kx columns per tile of the y and z passes
 constexpr int kS3MaxLen = 1024;
-constexpr int kS3ColElems = kS3T * kS3MaxLen;
+constexpr int kS3ColElems = 4096;  // complex elements of a y or z tile, at most
+constexpr int kS3Pitch = 8;        // kx rows start on multiples of 8 complex values (128 bytes)
+
+// kx columns per tile of a y or z pass over lines of length n: 8, whole
+// 128-byte lines of a row (the z pass strides by a plane: with half lines it
+// took 338 instead of 169 us on 256^3, the y pass 208 instead of 149), where
+// two such tiles share the LDS of a CU, else 4.
+constexpr int s3_cols(int n) { return 8 * n <= kS3ColElems ? 8 : 4; }
 
 struct Spec3Args {
   const void* pool;
@@ -50,10 +56,10 @@ struct Spec3Args {
   int32_t sy, sz;        // state strides along y and z
   int32_t n[3];          // nx, ny, nz
   int32_t nh;            // nx / 2 + 1
-  int32_t ntk;           // tiles along kx: ceil(nh / kS3T)
+  int32_t np;            // row pitch of U and P: nh rounded up to kS3Pitch
   int32_t gx;            // x-lines per pass of the x kernel
   int32_t nb;            // shells
-  int64_t cplane;        // complex values per component plane: nz ny nh
+  int64_t cplane;        // complex values per component plane: nz ny np
   double2* U;            // 3 component planes [z][y][kx]
   double* P;             // power [ky][kz][kx]
   double* partials;      // [bin workgroup][shell]
@@ -137,7 +143,7 @@ __global__ void __launch_bounds__(kS3Block) spec3_x_kernel(Spec3Args a, FftPlan 
       const double2 zk = buf[fft_pad(lp * nx + k)];
       const double2 zm = conj2(buf[fft_pad(lp * nx + km)]);
       const double2 s = cadd(zk, zm), d = cmi(csub(zk, zm));
-      const int64_t o = (int64_t(z) * ny + y) * nh + k;
+      const int64_t o = (int64_t(z) * ny + y) * a.np + k;
       a.U[o] = make_double2(0.5 * s.x, 0.5 * s.y);
       a.U[o + a.cplane] = make_double2(0.5 * d.x, 0.5 * d.y);
       const int q = (G + (lp >> 1)) * nx;
@@ -149,45 +155,57 @@ __global__ void __launch_bounds__(kS3Block) spec3_x_kernel(Spec3Args a, FftPlan 
 }
 
 // FFT along y (ZP false: tile = (c, z, kx tile), in place) or z (ZP true:
-// tile = (ky, kx tile), the three components in turn, power out).
-template <bool ZP>
+// tile = (ky, kx tile), the three components in turn, power out).  E: complex
+// elements of a tile, at most (2048 or 4096).
+template <bool ZP, int E>
 __global__ void __launch_bounds__(kS3Block) spec3_col_kernel(Spec3Args a, FftPlan pl) {
   extern __shared__ double2 s3lds[];
-  const int nx = a.n[0], ny = a.n[1], nz = a.n[2], nh = a.nh, L = pl.n, ls = L + 1;
+  const int nx = a.n[0], ny = a.n[1], nz = a.n[2], nh = a.nh, np = a.np, L = pl.n, ls = L + 1;
+  const int T = s3_cols(L), lt = T == 8 ? 3 : 2, ntk = (nh + T - 1) >> lt;
   double2* W = s3lds;
   double2* buf = s3lds + L;
   const double2* tw = a.tw + (ZP ? nx + ny : nx);
   for (int t = threadIdx.x; t < L; t += kS3Block) W[t] = tw[t];
-  const int nt = (ZP ? ny : 3 * nz) * a.ntk;
+  const int nt = (ZP ? ny : 3 * nz) * ntk;
   const int tile = xcd_tile(int(blockIdx.x), nt);
-  const int o = tile / a.ntk, kx0 = (tile - o * a.ntk) * kS3T;
+  const int o = tile / ntk, kx0 = (tile - o * ntk) << lt;
   // line element j of column t at col[j S + t]
-  const int64_t S = ZP ? int64_t(ny) * nh : int64_t(nh);
-  constexpr int EPT = kS3ColElems / kS3Block;
+  const int64_t S = ZP ? int64_t(ny) * np : int64_t(np);
+  constexpr int EPT = E / kS3Block;
   double pw[ZP ? EPT : 1];
 #pragma unroll
   for (int i = 0; i < (ZP ? EPT : 1); ++i) pw[i] = 0.0;
-  for (int c = 0; c < (ZP ? 3 : 1); ++c) {
-    double2* col = ZP ? a.U + c * a.cplane + int64_t(o) * nh + kx0
-                      : a.U + int64_t(o) * ny * nh + kx0;
-    __syncthreads();  // the twiddles, and the previous component's reads of buf
-    double2 v[EPT];
+  double2 v[EPT];
+  auto fetch = [&](int c) {
+    const double2* col = ZP ? a.U + c * a.cplane + int64_t(o) * np + kx0
+                            : a.U + int64_t(o) * ny * np + kx0;
 #pragma unroll
     for (int i = 0; i < EPT; ++i) {
-      const int e = threadIdx.x + i * kS3Block, t = e & (kS3T - 1), j = e / kS3T;
+      const int e = threadIdx.x + i * kS3Block, t = e & (T - 1), j = e >> lt;
       v[i] = make_double2(0.0, 0.0);
       if (j < L && kx0 + t < nh) v[i] = col[j * S + t];
     }
+  };
+  // the next component's loads are in flight during this one's transform
+  // where a thread holds few elements (with 16 of them the registers leave
+  // one wave per SIMD)
+  constexpr bool kAhead = ZP && E <= 2048;
+  if (kAhead) fetch(0);
+  for (int c = 0; c < (ZP ? 3 : 1); ++c) {
+    __syncthreads();  // the twiddles, and the previous component's reads of buf
+    if (!kAhead) fetch(c);
 #pragma unroll
     for (int i = 0; i < EPT; ++i) {
-      const int e = threadIdx.x + i * kS3Block, t = e & (kS3T - 1), j = e / kS3T;
+      const int e = threadIdx.x + i * kS3Block, t = e & (T - 1), j = e >> lt;
       if (j < L) buf[fft_pad(t * ls + j)] = v[i];
     }
+    if (kAhead && c < 2) fetch(c + 1);
     __syncthreads();
-    fft_lines_inplace<kS3ColElems, kS3Block>(buf, kS3T, ls, pl, W);
+    fft_lines_inplace<E, kS3Block>(buf, T, ls, pl, W);
+    double2* col = a.U + int64_t(o) * ny * np + kx0;
 #pragma unroll
     for (int i = 0; i < EPT; ++i) {
-      const int e = threadIdx.x + i * kS3Block, t = e & (kS3T - 1), j = e / kS3T;
+      const int e = threadIdx.x + i * kS3Block, t = e & (T - 1), j = e >> lt;
       if (j < L && kx0 + t < nh) {
         const double2 u = buf[fft_pad(t * ls + j)];
         if (ZP)
@@ -200,14 +218,25 @@ __global__ void __launch_bounds__(kS3Block) spec3_col_kernel(Spec3Args a, FftPla
   if (ZP) {
 #pragma unroll
     for (int i = 0; i < EPT; ++i) {
-      const int e = threadIdx.x + i * kS3Block, t = e & (kS3T - 1), j = e / kS3T;
+      const int e = threadIdx.x + i * kS3Block, t = e & (T - 1), j = e >> lt;
       const int kx = kx0 + t;
       if (j < L && kx < nh) {
         const double w = (kx == 0 || 2 * kx == nx) ? 1.0 : 2.0;
-        a.P[(int64_t(o) * nz + j) * nh + kx] = w * pw[i];
+        a.P[(int64_t(o) * nz + j) * np + kx] = w * pw[i];
       }
     }
   }
+}
+
+template <bool ZP>
+static void launch_s3_cols(const Spec3Args& a, const FftPlan& pl, hipStream_t st) {
+  const int T = s3_cols(pl.n), ntk = (a.nh + T - 1) / T;
+  const dim3 grid(unsigned((ZP ? a.n[1] : 3 * a.n[2]) * ntk));
+  const size_t lds = size_t(pl.n + fft_lds(T * (pl.n + 1))) * sizeof(double2);
+  if (T * pl.n <= 2048)
+    hipLaunchKernelGGL((spec3_col_kernel<ZP, 2048>), grid, dim3(kS3Block), lds, st, a, pl);
+  else
+    hipLaunchKernelGGL((spec3_col_kernel<ZP, kS3ColElems>), grid, dim3(kS3Block), lds, st, a, pl);
 }
 
 // Shell of the integer wavevector with |k|^2 = m2: round(sqrt(m2)), taken
@@ -233,7 +262,7 @@ __global__ void __launch_bounds__(kS3Block) spec3_bin_kernel(Spec3Args a) {
     const int ky = int(a.dnz.div(uint32_t(r))), kz = int(r) - ky * nz;
     const int sy = 2 * ky <= ny ? ky : ky - ny, sz = 2 * kz <= nz ? kz : kz - nz;
     const int myz = sy * sy + sz * sz;
-    const double* row = a.P + r * nh;
+    const double* row = a.P + r * a.np;
     for (int c0 = 0; c0 < nh; c0 += 64) {
       const int kx = c0 + lane;
       const bool valid = kx < nh;
@@ -274,6 +303,9 @@ __global__ void __launch_bounds__(kS3Block) spec3_final_kernel(const double* par
   }
 }
 
+// Row pitch of the half spectra of lines of nx cells.
+static int s3_pitch(int nx) { return (nx / 2 + kS3Pitch) / kS3Pitch * kS3Pitch; }
+
 // Regions of the workspace, each 256-byte aligned.
 static size_t s3_align(size_t b) { return (b + 255) & ~size_t(255); }
 
@@ -294,8 +326,7 @@ bool spec3_shape_ok(const PatchDev& P) {
 }
 
 size_t spec3_workspace_bytes(const PatchDev& P, int* nb) {
-  const int64_t nh = P.n[0] / 2 + 1;
-  const int64_t cells = nh * P.n[1] * P.n[2];
+  const int64_t cells = int64_t(s3_pitch(P.n[0])) * P.n[1] * P.n[2];
   const int shells = shell_count_host(P.n);
   if (nb) *nb = shells;
   return s3_align(size_t(3 * cells) * sizeof(double2)) + s3_align(size_t(cells) * sizeof(double)) +
@@ -317,10 +348,10 @@ static hipError_t launch_s3(const LaunchSpec3& L, hipStream_t st) {
   a.sz = P.sz;
   for (int i = 0; i < 3; ++i) a.n[i] = P.n[i];
   a.nh = P.n[0] / 2 + 1;
-  a.ntk = (a.nh + kS3T - 1) / kS3T;
+  a.np = s3_pitch(P.n[0]);
   a.gx = std::max(1, (kS3Elems / 2) / P.n[0]);
   a.nb = shell_count_host(P.n);
-  a.cplane = int64_t(a.nh) * P.n[1] * P.n[2];
+  a.cplane = int64_t(a.np) * P.n[1] * P.n[2];
   char* w = static_cast<char*>(L.work);
   a.U = reinterpret_cast<double2*>(w);
   w += s3_align(size_t(3 * a.cplane) * sizeof(double2));
@@ -344,13 +375,9 @@ static hipError_t launch_s3(const LaunchSpec3& L, hipStream_t st) {
   const size_t xlds = size_t(P.n[0] + fft_lds((a.gx + (a.gx + 1) / 2) * P.n[0])) * sizeof(double2);
   hipLaunchKernelGGL(spec3_x_kernel<T>, dim3(unsigned(xgrid)), dim3(kS3Block), xlds, st, a, px);
   if ((e = hipGetLastError()) != hipSuccess) return e;
-  const size_t ylds = size_t(P.n[1] + fft_lds(kS3T * (P.n[1] + 1))) * sizeof(double2);
-  hipLaunchKernelGGL(spec3_col_kernel<false>, dim3(unsigned(3 * P.n[2] * a.ntk)), dim3(kS3Block),
-                     ylds, st, a, py);
+  launch_s3_cols<false>(a, py, st);
   if ((e = hipGetLastError()) != hipSuccess) return e;
-  const size_t zlds = size_t(P.n[2] + fft_lds(kS3T * (P.n[2] + 1))) * sizeof(double2);
-  hipLaunchKernelGGL(spec3_col_kernel<true>, dim3(unsigned(P.n[1] * a.ntk)), dim3(kS3Block), zlds,
-                     st, a, pz);
+  launch_s3_cols<true>(a, pz, st);
   if ((e = hipGetLastError()) != hipSuccess) return e;
   hipLaunchKernelGGL(spec3_bin_kernel, dim3(unsigned(kSpec3BinBlocks)), dim3(kS3Block),
                      size_t(kS3Block / 64) * a.nb * sizeof(double), st, a);
