@@ -473,8 +473,10 @@ int hydro_amr_prolong(hydro_ctx* c, const hydro_amr_link* links, int32_t n, int 
  * recomputed before its next HYDRO_DT_CFL step.  The workspace (256-byte
  * aligned, hydro_amr_step_workspace_bytes) holds the start-of-step copy of
  * the coarse cells that prolongation reads (at the coarse pool's offsets, so
- * it is as large as the pool), the registers and the link table.  Asynchronous.  Errors: HYDRO_EINVAL, HYDRO_ESTATE
- * (not batches, work lists out of date), HYDRO_EDEVICE. */
+ * it is as large as the pool), the registers, the fluxes of one fine substep
+ * through the fine patches' faces and the link table.  Asynchronous.  Errors:
+ * HYDRO_EINVAL, HYDRO_ESTATE (not batches, work lists out of date),
+ * HYDRO_EDEVICE. */
 #define HYDRO_AMR_NO_REFLUX 0x1u
 
 /* The largest stable coarse dt of the two-level step: min(coarse CFL dt,

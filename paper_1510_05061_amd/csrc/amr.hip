@@ -76,6 +76,8 @@ struct AmrArgs {
   int link0, maxface;
   int axis, side, fine;
   double dt, weight, gamma, grav;
+  const T* face;
+  int nface;
   const AmrLink* dlinks;
 };
 
@@ -593,6 +595,39 @@ __global__ void __launch_bounds__(kAmrBlock) flux_reg_kernel(AmrArgs<T> a) {
 }
 static_assert(kAmrBlock % 16 == 0, "whole lane groups per workgroup");
 
+// Fine flux registers of link blockIdx.y, axis blockIdx.z / 2, side
+// blockIdx.z mod 2, from the fine face fluxes that the sweeps wrote (sweep
+// frame, a.face): one coarse face per thread, the mean of its four fine faces
+// summed in (t2, t1) order, times a.weight.
+template <class T>
+__global__ void __launch_bounds__(kAmrBlock) flux_gather_kernel(AmrArgs<T> a) {
+  const AmrLink L = link_of(a, int(blockIdx.y));
+  const int axis = int(blockIdx.z >> 1), side = int(blockIdx.z & 1);
+  const PatchDev F = fine_patch(a.fpatches, L.fine, a.finset);
+  const int n1 = ext(F, t1_of(axis)), m1 = n1 / 2, nface = m1 * (ext(F, t2_of(axis)) / 2);
+  double* reg = a.reg + a.nreg +
+                (((int64_t(a.link0) + blockIdx.y) * 3 + axis) * 2 + side) * a.maxface * 5;
+  const T* f = a.face + int64_t((L.fine * 3 + axis) * 2 + side) * 5 * a.nface;
+  for (int fc = blockIdx.x * kAmrBlock + threadIdx.x; fc < nface; fc += gridDim.x * kAmrBlock) {
+    const int j2 = fc / m1, j1 = fc - j2 * m1;
+    const T* q = f + int64_t(2 * j2) * n1 + 2 * j1;
+    double x[5][4];
+#pragma unroll
+    for (int v = 0; v < 5; ++v) {
+      const T* p = q + int64_t(v) * a.nface;
+      x[v][0] = double(p[0]);
+      x[v][1] = double(p[1]);
+      x[v][2] = double(p[n1]);
+      x[v][3] = double(p[n1 + 1]);
+    }
+#pragma unroll
+    for (int v = 0; v < 5; ++v) {
+      const double s = ((x[v][0] + x[v][1]) + x[v][2]) + x[v][3];
+      reg[int64_t(fc) * 5 + lab_var(axis, v)] += a.weight * (0.25 * s);
+    }
+  }
+}
+
 // Refluxing of link blockIdx.y across its a.side faces along a.axis.
 template <class T>
 __global__ void __launch_bounds__(kAmrBlock) reflux_kernel(AmrArgs<T> a) {
@@ -657,6 +692,8 @@ static AmrArgs<T> to_aargs(const LaunchAmr& L) {
   a.weight = L.weight;
   a.gamma = L.gamma;
   a.grav = L.grav;
+  a.face = static_cast<const T*>(L.face);
+  a.nface = L.nface;
   a.dlinks = L.dlinks;
   return a;
 }
@@ -713,6 +750,9 @@ static hipError_t launch_amr_t(const LaunchAmr& L, hipStream_t st) {
   } else if (L.op == kAmrFlux) {
     hipLaunchKernelGGL(flux_reg_kernel<T>, dim3(amr_blocks(L.cells), unsigned(L.nlinks), 2u),
                        dim3(kAmrBlock), 0, st, a);
+  } else if (L.op == kAmrGather) {
+    hipLaunchKernelGGL(flux_gather_kernel<T>, dim3(amr_blocks(L.cells), unsigned(L.nlinks), 6u),
+                       dim3(kAmrBlock), 0, st, a);
   } else {
     hipLaunchKernelGGL(reflux_kernel<T>, dim3(amr_blocks(L.cells), unsigned(L.nlinks)),
                        dim3(kAmrBlock), 0, st, a);
@@ -721,12 +761,13 @@ static hipError_t launch_amr_t(const LaunchAmr& L, hipStream_t st) {
 }
 
 hipError_t launch_amr(const LaunchAmr& L, hipStream_t st) {
-  if (L.op < kAmrFill || L.op > kAmrSnapshot) return hipErrorInvalidValue;
+  if (L.op < kAmrFill || L.op > kAmrGather) return hipErrorInvalidValue;
   if (L.op == kAmrSnapshot && (!L.cold || L.margin < 0)) return hipErrorInvalidValue;
   if (L.op != kAmrFill &&
       (!L.patches || L.nlinks < 1 || (!L.dlinks && L.nlinks > kAmrLinksPerLaunch) ||
        L.nlinks > 65535))
     return hipErrorInvalidValue;
+  if (L.op == kAmrGather && (!L.reg || !L.face || L.maxface < 1)) return hipErrorInvalidValue;
   if ((L.op == kAmrFlux || L.op == kAmrReflux) &&
       (!L.reg || L.maxface < 1 || L.axis < 0 || L.axis > 2 || L.side < 0 || L.side > 1))
     return hipErrorInvalidValue;

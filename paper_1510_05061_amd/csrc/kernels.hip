@@ -25,6 +25,8 @@
 // communication each timestep" of the paper's section "Capabilities needed".
 #include <hip/hip_runtime.h>
 
+#include <type_traits>
+
 #include "euler.hpp"
 #include "fastdiv.hpp"
 #include "launch.hpp"
@@ -54,6 +56,8 @@ struct SweepArgs {
   int32_t tail;              // direct launches with totals: kTailNone, kTailSum or kTailStep
   const double* pdt;         // persistent: dt per patch (null: scal->dt)
   unsigned long long* psmax; // persistent: CFL maximum per patch
+  T* face;                   // REG kernels: face fluxes of the patches (FaceOut)
+  int32_t nface, inset;      // REG kernels: faces per side, layers outside the faces
   T* dst;                    // out-of-place result (null: pool, in place)
   const WinDev* wins;        // window sweeps: the windows of a z-plane
   int32_t nwin;
@@ -496,6 +500,46 @@ __device__ __forceinline__ Prim<T> get_prim(const T* s) {
   return W;
 }
 
+// Fluxes through the faces of the box `inset` layers inside a patch (the
+// interior of a fine patch's stored box), written by the REG instantiations
+// of the batch sweeps as they compute them, for the flux registers of a level
+// step: component v (sweep frame) of side s of axis d of patch p, face
+// (t2, t1) of the transverse box at
+//   face[(((p 3 + d) 2 + s) 5 + v) nface + t2 m1 + t1],  m1 its extent along t1.
+struct NoFaces {
+  template <class T>
+  __device__ __forceinline__ void put(int, const Cons<T>&) const {}
+};
+template <class T>
+struct FaceOut {
+  T* p;        // (patch, axis, side 0, component 0) at this pencil's face (null: none)
+  int64_t ns;  // elements per component; five to a side
+  int lo, hi;  // faces: left faces of these cells
+  __device__ __forceinline__ FaceOut(const SweepArgs<T>& a, const PatchDev& P, int patch, int axis,
+                                     int i1, int i2) {
+    const int a1 = axis == 0 ? 1 : 0, a2 = axis == 2 ? 1 : 2;
+    const int g = a.inset, m1 = P.n[a1] - 2 * g, m2 = P.n[a2] - 2 * g;
+    lo = g;
+    hi = P.n[axis] - g;
+    ns = a.nface;
+    const int t1 = i1 - g, t2 = i2 - g;
+    p = t1 >= 0 && t1 < m1 && t2 >= 0 && t2 < m2
+            ? a.face + int64_t(patch * 3 + axis) * 10 * ns + int64_t(t2) * m1 + t1
+            : nullptr;
+  }
+  // F: the flux through the left face of cell i
+  __device__ __forceinline__ void put(int i, const Cons<T>& F) const {
+    if (p && (i == lo || i == hi)) {
+      T* q = p + (i == lo ? 0 : 5 * ns);
+      q[0] = F.r;
+      q[ns] = F.mn;
+      q[2 * ns] = F.mt1;
+      q[3 * ns] = F.mt2;
+      q[4 * ns] = F.e;
+    }
+  }
+};
+
 // Lane-run update of a pencil that lies inside one wave.  This lane holds V
 // consecutive cells U (rotated frame: mn is the momentum along the sweep
 // axis, AXIS); gl is its place in the pencil (0 .. last), srcL and srcR the
@@ -503,12 +547,13 @@ __device__ __forceinline__ Prim<T> get_prim(const T* s) {
 // other's neighbours).  Values cross lanes by shuffles only; the ends of a
 // non-periodic pencil build their ghost cells from their own cells.  U is
 // replaced by the updated state; lanes with `act` fold their cells into the
-// CFL maximum when do_cfl.  Every lane of the wave must call this together.
-template <class T, int V, int AXIS>
+// CFL maximum when do_cfl and show the fluxes of their left faces to `faces`.  Every lane of the wave must call this together.
+template <class T, int V, int AXIS, class Faces = NoFaces>
 __device__ __forceinline__ void lanerun_update(Cons<T> (&U)[V], int gl, int last, int srcL,
                                                int srcR, int bc_lo, int bc_hi,
                                                const SweepConst<T>& k, const T id[3], bool act,
-                                               bool do_cfl, T& smax, bool& bad) {
+                                               bool do_cfl, T& smax, bool& bad,
+                                               const Faces& faces = Faces{}) {
   Prim<T> W[V];
 #pragma unroll
   for (int c = 0; c < V; ++c) W[c] = to_prim(U[c], k);
@@ -546,6 +591,10 @@ __device__ __forceinline__ void lanerun_update(Cons<T> (&U)[V], int gl, int last
   Cons<T> F[V];
 #pragma unroll
   for (int c = 0; c < V; ++c) F[c] = hllc(c == 0 ? WpL : Wp[c - 1], Wm[c], k);
+  if (act) {
+#pragma unroll
+    for (int c = 0; c < V; ++c) faces.put(gl * V + c, F[c]);
+  }
 
   Cons<T> FR = shfl_cons(F[0], srcR);  // flux at the right face of the last cell
   if (gl == last && bc_hi != kBcPeriodic) {
@@ -1307,6 +1356,7 @@ struct PatchPlane {
   const SweepArgs<T>& a;
   const PatchDev& P;
   int z;
+  int patch;
   __device__ int n(int axis) const { return P.n[axis]; }
   __device__ int bc_lo(int axis) const { return axis == 0 ? a.bc_lo : a.bc_lo_y; }
   __device__ int bc_hi(int axis) const { return axis == 0 ? a.bc_hi : a.bc_hi_y; }
@@ -1450,7 +1500,7 @@ __device__ __forceinline__ void plane_run(T* lds, int x0, int y0, Cons<T> (&U)[V
 // a y-first step straight to memory (GDST, the written part only): a row
 // run is a coalesced vector access, so those two sweeps skip a copy through
 // LDS.  Only runs in the written part fold the CFL maximum and the totals.
-template <class T, int V, int AXIS, bool GSRC, bool GDST, bool TOT = false, class M>
+template <class T, int V, int AXIS, bool GSRC, bool GDST, bool TOT = false, bool REG = false, class M>
 __device__ void plane_sweep(const SweepArgs<T>& a, const M& m, const PatchDev& P, int p0, int p1,
                             T* lds, bool do_cfl, double dt, T& smax, bool& bad,
                             TotR* tot = nullptr) {
@@ -1493,8 +1543,14 @@ __device__ void plane_sweep(const SweepArgs<T>& a, const M& m, const PatchDev& P
     }
     if (GSRC && gl < LPP && pen + mstep < p1)
       row_run_off<T, V, false>(sb, m.off(gl * V, pen + mstep), Un);
-    lanerun_update<T, V, AXIS>(U, act ? gl : 0, last, srcL, srcR, blo, bhi, k, id, wr, do_cfl,
-                               smax, bad);
+    if constexpr (REG) {
+      const FaceOut<T> faces(a, P, m.patch, AXIS, pen, m.z);
+      lanerun_update<T, V, AXIS>(U, act ? gl : 0, last, srcL, srcR, blo, bhi, k, id, wr, do_cfl,
+                                 smax, bad, faces);
+    } else {
+      lanerun_update<T, V, AXIS>(U, act ? gl : 0, last, srcL, srcR, blo, bhi, k, id, wr, do_cfl,
+                                 smax, bad);
+    }
     if (TOT && wr) {
 #pragma unroll
       for (int c = 0; c < V; ++c) {
@@ -1533,16 +1589,16 @@ __device__ void plane_totals(const SweepArgs<T>& a, const M& m, const PatchDev& 
 // last launch of a step): y then x adds each written cell to the totals as
 // it stores it; x then y adds the written part in LDS with plane_totals
 // before copying it out.  `P` gives the cell widths and gravity frame.
-template <class T, int V, bool XFIRST, bool TOT, class M>
+template <class T, int V, bool XFIRST, bool TOT, bool REG = false, class M>
 __device__ __forceinline__ void plane_item(const SweepArgs<T>& a, const M& m, const PatchDev& P,
                                            T* lds, double dt, T& smax, bool& bad, TotR& tot) {
   const bool store = !(TOT && a.tonly);
   if (XFIRST) {
     // x: memory -> registers -> LDS; y: LDS -> LDS; then LDS -> memory
-    plane_sweep<T, V, 0, true, false>(a, m, P, 0, m.n(1), lds, false, dt, smax, bad);
+    plane_sweep<T, V, 0, true, false, false, REG>(a, m, P, 0, m.n(1), lds, false, dt, smax, bad);
     __syncthreads();
-    plane_sweep<T, V, 1, false, false>(a, m, P, m.lo(0), m.hi(0), lds, a.do_cfl != 0, dt, smax,
-                                       bad);
+    plane_sweep<T, V, 1, false, false, false, REG>(a, m, P, m.lo(0), m.hi(0), lds, a.do_cfl != 0,
+                                                   dt, smax, bad);
     __syncthreads();
     if (TOT) plane_totals<T, V>(a, m, P, lds, tot);
     if (store) plane_copy<T, V, false>(m, lds);
@@ -1550,10 +1606,10 @@ __device__ __forceinline__ void plane_item(const SweepArgs<T>& a, const M& m, co
     // memory -> LDS; y: LDS -> LDS; x: LDS -> registers -> memory
     plane_copy<T, V, true>(m, lds);
     __syncthreads();
-    plane_sweep<T, V, 1, false, false>(a, m, P, 0, m.n(0), lds, false, dt, smax, bad);
+    plane_sweep<T, V, 1, false, false, false, REG>(a, m, P, 0, m.n(0), lds, false, dt, smax, bad);
     __syncthreads();
     // (with TOT adding each written cell to the totals)
-    plane_sweep<T, V, 0, false, true, TOT>(a, m, P, m.lo(1), m.hi(1), lds, a.do_cfl != 0, dt,
+    plane_sweep<T, V, 0, false, true, TOT, REG>(a, m, P, m.lo(1), m.hi(1), lds, a.do_cfl != 0, dt,
                                            smax, bad, &tot);
   }
   __syncthreads();  // the LDS is free again
@@ -1563,7 +1619,7 @@ __device__ __forceinline__ void plane_item(const SweepArgs<T>& a, const M& m, co
 // in plane_item).  The plane takes up to half the LDS of a CU, so two
 // workgroups share one: no static LDS beside it (the totals reduction and
 // the next ticket use the plane's LDS once the plane has been copied out).
-template <class T, int V, bool XFIRST, bool TOT>
+template <class T, int V, bool XFIRST, bool TOT, bool REG = false>
 __global__ void __launch_bounds__(512) sweep_plane_kernel(SweepArgs<T> a) {
   extern __shared__ __align__(16) unsigned char dyn_lds[];
   T* lds = reinterpret_cast<T*>(dyn_lds);
@@ -1579,8 +1635,8 @@ __global__ void __launch_bounds__(512) sweep_plane_kernel(SweepArgs<T> a) {
     if (it >= a.nitems) break;
     const WorkItem w = a.items[it];
     const PatchDev P = a.patches[w.patch];
-    const PatchPlane<T> m{a, P, w.tile};
-    plane_item<T, V, XFIRST, TOT>(a, m, P, lds, item_dt(a, w.patch, dt0), smax, bad, tot);
+    const PatchPlane<T> m{a, P, w.tile, w.patch};
+    plane_item<T, V, XFIRST, TOT, REG>(a, m, P, lds, item_dt(a, w.patch, dt0), smax, bad, tot);
     if (TOT)
       tot_block_wide(tot, cell_volume(P), a.tpart + 6 * int64_t(it),
                      reinterpret_cast<double*>(dyn_lds), grav);
@@ -1704,9 +1760,10 @@ __device__ __forceinline__ int edge_slot(int c, int L, int N, int* seg) {
 //    read from memory once.
 //  * LDSH = false: each thread loads its halo cells from memory before the
 //    barrier (the owner loads them again when it marches there).
-template <class T, int AXIS, bool LDSH, bool TOT>
+template <class T, int AXIS, bool LDSH, bool TOT, bool REG = false>
 __device__ void colsweep_tile(const SweepArgs<T>& a, const PatchDev& P, int64_t tile,
-                              const SweepConst<T>& k, T* tab, T& smax, bool& bad, TotL& tot) {
+                              const SweepConst<T>& k, T* tab, T& smax, bool& bad, TotL& tot,
+                              int patch = 0) {
   const bool store = !(TOT && a.tonly);
   constexpr int TA = AXIS == 1 ? 2 : 1;   // the other transverse axis
   const int N = P.n[AXIS];
@@ -1830,6 +1887,10 @@ __device__ void colsweep_tile(const SweepArgs<T>& a, const PatchDev& P, int64_t 
   face_states(H[1], W0, W1, k, k.kick, WmC, WpC);           // cell ja
   Cons<T> Fl = hllc(WpPrev, WmC, k);
   WpPrev = WpC;
+  std::conditional_t<REG, FaceOut<T>, NoFaces> faces = [&] {
+    if constexpr (REG) return FaceOut<T>(a, P, patch, AXIS, cx, ct);
+    else return NoFaces{};
+  }();
 
   // one step of the march with cell j+2 in U2 (cell j updated)
   auto advance = [&](const Cons<T>& U2, int j) {
@@ -1837,6 +1898,7 @@ __device__ void colsweep_tile(const SweepArgs<T>& a, const PatchDev& P, int64_t 
     Prim<T> Wm1, Wp1;
     face_states(W0, W1, W2, k, k.kick, Wm1, Wp1);  // cell j+1
     const Cons<T> Fr = hllc(WpPrev, Wm1, k);
+    faces.put(j, Fl);
     update(U0, Fl, Fr, k);
     if (store) pd.store(b, U0);
     if (a.do_cfl) smax = fmax_(smax, cell_speed<T, AXIS>(U0, k, id, bad));
@@ -1892,6 +1954,7 @@ __device__ void colsweep_tile(const SweepArgs<T>& a, const PatchDev& P, int64_t 
     Prim<T> Wm1, Wp1;
     face_states(W0, W1, W2, k, (j + 1 == jb) ? kick_hi : k.kick, Wm1, Wp1);  // cell j+1
     const Cons<T> Fr = hllc(WpPrev, Wm1, k);
+    faces.put(j, Fl);
     update(U0, Fl, Fr, k);
     if (store) pd.store(b, U0);
     if (a.do_cfl) smax = fmax_(smax, cell_speed<T, AXIS>(U0, k, id, bad));
@@ -1915,7 +1978,7 @@ constexpr int kColWaves = HYDRO_COL_WAVES;
 // thread) first, then with LDSH the halo table.
 // FP32: kColWaves waves per SIMD; the persistent totals instantiation (the
 // batch's last z sweep) takes three, whose registers hold it without spills.
-template <class T, int AXIS, bool PERSIST, bool LDSH, bool TOT>
+template <class T, int AXIS, bool PERSIST, bool LDSH, bool TOT, bool REG = false>
 __global__ void __launch_bounds__(512, sizeof(T) == 4 ? (PERSIST && TOT ? 3 : kColWaves) : 1)
     sweep_col_kernel(SweepArgs<T> a) {
   __shared__ int item_s;
@@ -1941,7 +2004,7 @@ __global__ void __launch_bounds__(512, sizeof(T) == 4 ? (PERSIST && TOT ? 3 : kC
       const WorkItem w = a.items[it];
       const PatchDev P = a.patches[w.patch];
       SweepConst<T> k = make_const<T>(item_dt(a, w.patch, dt), P.dx[AXIS], a.gamma, a.grav);
-      colsweep_tile<T, AXIS, LDSH, TOT>(a, P, w.tile, k, tab, smax, bad, tot);
+      colsweep_tile<T, AXIS, LDSH, TOT, REG>(a, P, w.tile, k, tab, smax, bad, tot, w.patch);
       __syncthreads();
       if (TOT) tot_block(tot, cell_volume(P), a.tpart + 6 * int64_t(it), tred, grav);
       item_cfl(a, w.patch, smax, red);
@@ -2227,6 +2290,9 @@ static SweepArgs<T> to_args(const LaunchSweep& L) {
   a.pdt = L.pdt;
   a.tail = L.tail;
   a.psmax = L.psmax;
+  a.face = static_cast<T*>(L.face);
+  a.nface = L.nface;
+  a.inset = L.inset;
   a.dst = static_cast<T*>(L.dst);
   a.wins = L.wins;
   a.nwin = L.nwin;
@@ -2312,6 +2378,16 @@ static hipError_t launch_col(const LaunchSweep& L, hipStream_t st, dim3 grid) {
   const size_t tl = TOT ? size_t(threads) * kTotStride * sizeof(double) : 0;  // totals (TotL)
   SweepArgs<T> a = to_args<T>(L);
   a.s = s;
+  if constexpr (PERSIST && !TOT) {
+    if (L.face) {  // the level step's z sweep
+      if (L.axis != 2) return hipErrorInvalidValue;
+      if (ldsh)
+        hipLaunchKernelGGL((sweep_col_kernel<T, 2, true, true, false, true>), grid, block, tab, st, a);
+      else
+        hipLaunchKernelGGL((sweep_col_kernel<T, 2, true, false, false, true>), grid, block, 0, st, a);
+      return hipGetLastError();
+    }
+  }
   if (L.axis == 1) {
     if (ldsh)
       hipLaunchKernelGGL((sweep_col_kernel<T, 1, PERSIST, true, TOT>), grid, block, tl + tab, st,
@@ -2333,6 +2409,17 @@ static hipError_t launch_plane_v(const LaunchSweep& L, hipStream_t st) {
   const SweepArgs<T> a = to_args<T>(L);
   // with totals the plane's LDS also takes the per-item reduction
   const size_t lds = std::max(size_t(L.plane_lds), TOT ? size_t(kTotWideBytes) * L.cfg.block : 0);
+  if constexpr (!TOT) {
+    if (L.face) {  // the level step
+      if (L.plane == kPlaneXY)
+        hipLaunchKernelGGL((sweep_plane_kernel<T, V, true, false, true>), dim3(L.nblocks),
+                           dim3(L.cfg.block), lds, st, a);
+      else
+        hipLaunchKernelGGL((sweep_plane_kernel<T, V, false, false, true>), dim3(L.nblocks),
+                           dim3(L.cfg.block), lds, st, a);
+      return hipGetLastError();
+    }
+  }
   if (L.plane == kPlaneXY)
     hipLaunchKernelGGL((sweep_plane_kernel<T, V, true, TOT>), dim3(L.nblocks),
                        dim3(L.cfg.block), lds, st, a);

@@ -62,6 +62,11 @@ struct LaunchSweep {
   // laid out like pool (null: in place); only the z march and the window
   // sweeps take one
   void* dst;
+  // the level step's sweeps of the fine level (persistent fused plane and z
+  // launches without totals): the fluxes through the faces of the box `inset`
+  // layers inside each patch go to `face`, nface of them per (axis, side)
+  void* face;
+  int32_t nface, inset;
   const WinDev* wins;  // window sweeps: the windows of a z-plane
   int32_t nwin;
 };
@@ -146,7 +151,7 @@ struct LaunchBurn {
 
 // AMR operators (amr.hip).
 constexpr int kAmrFill = 0, kAmrRestrict = 1, kAmrProlong = 2, kAmrFlux = 3, kAmrReflux = 4,
-              kAmrSnapshot = 5;
+              kAmrSnapshot = 5, kAmrGather = 6;
 constexpr int kAmrLinksPerLaunch = 128;  // links passed by value in the kernel arguments
 constexpr int kAmrMaxBlocks = 4096;
 
@@ -195,6 +200,8 @@ struct LaunchAmr {
   double dt;                         // kAmrFlux: sweep length
   double weight;                     // kAmrFlux: register += weight * flux
   double gamma, grav;                // kAmrFlux: sweep constants (gravity along axis)
+  const void* face;                  // kAmrGather: fine face fluxes (LaunchSweep::face)
+  int32_t nface;
   // device link table (null: `links`); with it one launch takes nlinks links
   // and link l of the launch is table entry l
   const AmrLink* dlinks;
