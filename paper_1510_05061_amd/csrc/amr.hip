@@ -464,8 +464,8 @@ __device__ __forceinline__ void face_flux(const T* p0, const PatchDev& P, int ax
     W[m] = to_prim(U, k);
   }
   Prim<T> Wm0, Wp0, Wm1, Wp1;
-  face_states(W[0], W[1], W[2], k, k.kick, Wm0, Wp0);  // cell f - 1
-  face_states(W[1], W[2], W[3], k, k.kick, Wm1, Wp1);  // cell f
+  face_states(W[0], W[1], W[2], k, k.gk, Wm0, Wp0);  // cell f - 1
+  face_states(W[1], W[2], W[3], k, k.gk, Wm1, Wp1);  // cell f
   const Cons<T> F = hllc(Wp0, Wm1, k);
   out[0] = double(F.r);
   out[1] = double(F.mn);
@@ -541,7 +541,7 @@ __global__ void __launch_bounds__(kAmrBlock) flux_reg_kernel(AmrArgs<T> a) {
       Wr.p = __shfl(W.p, l + 1, 16);
       Wr.ri = T(0);
       Prim<T> Wm, Wp;
-      face_states(Wl, W, Wr, k, k.kick, Wm, Wp);
+      face_states(Wl, W, Wr, k, k.gk, Wm, Wp);
       // lane m = 2 takes W+ of cell f - 1 from lane m = 1
       Prim<T> L1;
       L1.r = __shfl(Wp.r, l - 1, 16);

@@ -568,14 +568,14 @@ __device__ __forceinline__ void lanerun_update(Cons<T> (&U)[V], int gl, int last
   for (int c = 0; c < V; ++c) {
     const Prim<T>& L = c == 0 ? Wl : W[c - 1];
     const Prim<T>& R = c == V - 1 ? Wr : W[c + 1];
-    face_states(L, W[c], R, k, k.kick, Wm[c], Wp[c]);
+    face_states(L, W[c], R, k, k.gk, Wm[c], Wp[c]);
   }
 
   Prim<T> WpL = shfl_prim(Wp[V - 1], srcL);  // face state W+ of the cell left of the first
   if (gl == 0 && bc_lo != kBcPeriodic) {
     // ghost cell -1 with ghost -2 behind it
     Prim<T> g1, g2, dummy;
-    T kick = k.kick;
+    T gk = k.gk;
     if (bc_lo == kBcOutflow) {
       g1 = W[0];
       g2 = W[0];
@@ -583,9 +583,9 @@ __device__ __forceinline__ void lanerun_update(Cons<T> (&U)[V], int gl, int last
       const Prim<T>& W1 = V >= 2 ? W[V >= 2 ? 1 : 0] : Wr;
       g1 = mirror(W[0]);
       g2 = mirror(W1);
-      kick = -k.kick;
+      gk = -k.gk;
     }
-    face_states(g2, g1, W[0], k, kick, dummy, WpL);
+    face_states(g2, g1, W[0], k, gk, dummy, WpL);
   }
 
   Cons<T> F[V];
@@ -600,7 +600,7 @@ __device__ __forceinline__ void lanerun_update(Cons<T> (&U)[V], int gl, int last
   if (gl == last && bc_hi != kBcPeriodic) {
     // ghost cell N with ghost N+1 beyond it
     Prim<T> g1, g2, WmR, dummy;
-    T kick = k.kick;
+    T gk = k.gk;
     if (bc_hi == kBcOutflow) {
       g1 = W[V - 1];
       g2 = W[V - 1];
@@ -608,9 +608,9 @@ __device__ __forceinline__ void lanerun_update(Cons<T> (&U)[V], int gl, int last
       const Prim<T>& Wn2 = V >= 2 ? W[V >= 2 ? V - 2 : 0] : Wl;
       g1 = mirror(W[V - 1]);
       g2 = mirror(Wn2);
-      kick = -k.kick;
+      gk = -k.gk;
     }
-    face_states(W[V - 1], g1, g2, k, kick, WmR, dummy);
+    face_states(W[V - 1], g1, g2, k, gk, WmR, dummy);
     FR = hllc(Wp[V - 1], WmR, k);
   }
 
@@ -758,7 +758,7 @@ __device__ void xsweep_tile(const SweepArgs<T>& a, const PatchDev& P, int64_t ti
   for (int c = 0; c < V; ++c) {
     const Prim<T>& L = c == 0 ? Wl : W[c - 1];
     const Prim<T>& R = c == V - 1 ? Wr : W[c + 1];
-    face_states(L, W[c], R, k, k.kick, Wm[c], Wp[c]);
+    face_states(L, W[c], R, k, k.gk, Wm[c], Wp[c]);
   }
 
   Prim<T> WpL = shfl_prim(Wp[V - 1], srcL);  // face state W+ of the cell left of the first
@@ -773,7 +773,7 @@ __device__ void xsweep_tile(const SweepArgs<T>& a, const PatchDev& P, int64_t ti
   if (gl == 0 && a.bc_lo != kBcPeriodic) {
     // ghost cell -1 with ghost -2 behind it
     Prim<T> g1, g2, dummy;
-    T kick = k.kick;
+    T gk = k.gk;
     if (a.bc_lo == kBcOutflow) {
       g1 = W[0];
       g2 = W[0];
@@ -781,9 +781,9 @@ __device__ void xsweep_tile(const SweepArgs<T>& a, const PatchDev& P, int64_t ti
       const Prim<T>& W1 = V >= 2 ? W[V >= 2 ? 1 : 0] : Wr;
       g1 = mirror(W[0]);
       g2 = mirror(W1);
-      kick = -k.kick;
+      gk = -k.gk;
     }
-    face_states(g2, g1, W[0], k, kick, dummy, WpL);
+    face_states(g2, g1, W[0], k, gk, dummy, WpL);
   }
 
   Cons<T> F[V];
@@ -807,7 +807,7 @@ __device__ void xsweep_tile(const SweepArgs<T>& a, const PatchDev& P, int64_t ti
   if (gl == last && a.bc_hi != kBcPeriodic) {
     // ghost cell N with ghost N+1 beyond it
     Prim<T> g1, g2, WmR, dummy;
-    T kick = k.kick;
+    T gk = k.gk;
     if (a.bc_hi == kBcOutflow) {
       g1 = W[V - 1];
       g2 = W[V - 1];
@@ -815,9 +815,9 @@ __device__ void xsweep_tile(const SweepArgs<T>& a, const PatchDev& P, int64_t ti
       const Prim<T>& Wn2 = V >= 2 ? W[V >= 2 ? V - 2 : 0] : Wl;
       g1 = mirror(W[V - 1]);
       g2 = mirror(Wn2);
-      kick = -k.kick;
+      gk = -k.gk;
     }
-    face_states(W[V - 1], g1, g2, k, kick, WmR, dummy);
+    face_states(W[V - 1], g1, g2, k, gk, WmR, dummy);
     FR = hllc(Wp[V - 1], WmR, k);
   }
 
@@ -1091,7 +1091,7 @@ __device__ void xmarch_pencils(const SweepArgs<T>& a, const PatchDev& P, int q0,
       for (int c = 0; c < V; ++c) {
         const Prim<T>& L = c == 0 ? Wl : W[c - 1];
         const Prim<T>& R = c == V - 1 ? Wr : W[c + 1];
-        face_states(L, W[c], R, k, k.kick, Wm[c], Wp[c]);
+        face_states(L, W[c], R, k, k.gk, Wm[c], Wp[c]);
       }
 
       Prim<T> WpL = shfl_prim(Wp[V - 1], srcL);
@@ -1100,11 +1100,11 @@ __device__ void xmarch_pencils(const SweepArgs<T>& a, const PatchDev& P, int q0,
           WpL = WpPrev;
         } else if (per) {
           Prim<T> dummy;
-          face_states(Wt2, Wt1, W[0], k, k.kick, dummy, WpL);
+          face_states(Wt2, Wt1, W[0], k, k.gk, dummy, WpL);
         } else {
           // ghost cell -1 with ghost -2 behind it
           Prim<T> g1, g2, dummy;
-          T kick = k.kick;
+          T gk = k.gk;
           if (a.bc_lo == kBcOutflow) {
             g1 = W[0];
             g2 = W[0];
@@ -1112,9 +1112,9 @@ __device__ void xmarch_pencils(const SweepArgs<T>& a, const PatchDev& P, int q0,
             const Prim<T>& W1 = V >= 2 ? W[V >= 2 ? 1 : 0] : Wr;
             g1 = mirror(W[0]);
             g2 = mirror(W1);
-            kick = -k.kick;
+            gk = -k.gk;
           }
-          face_states(g2, g1, W[0], k, kick, dummy, WpL);
+          face_states(g2, g1, W[0], k, gk, dummy, WpL);
         }
       }
 
@@ -1130,7 +1130,7 @@ __device__ void xmarch_pencils(const SweepArgs<T>& a, const PatchDev& P, int q0,
         } else {
           // ghost cell N with ghost N+1 beyond it
           Prim<T> g1, g2, WmR, dummy;
-          T kick = k.kick;
+          T gk = k.gk;
           if (a.bc_hi == kBcOutflow) {
             g1 = W[V - 1];
             g2 = W[V - 1];
@@ -1138,9 +1138,9 @@ __device__ void xmarch_pencils(const SweepArgs<T>& a, const PatchDev& P, int q0,
             const Prim<T>& Wn2 = V >= 2 ? W[V >= 2 ? V - 2 : 0] : Wl;
             g1 = mirror(W[V - 1]);
             g2 = mirror(Wn2);
-            kick = -k.kick;
+            gk = -k.gk;
           }
-          face_states(W[V - 1], g1, g2, k, kick, WmR, dummy);
+          face_states(W[V - 1], g1, g2, k, gk, WmR, dummy);
           FR = hllc(Wp[V - 1], WmR, k);
         }
       }
@@ -1860,8 +1860,8 @@ __device__ void colsweep_tile(const SweepArgs<T>& a, const PatchDev& P, int64_t 
 
   T id[3];
   inv_widths<T>(P, id);
-  const T kick_lo = (ja == 0 && a.bc_lo == kBcReflect) ? -k.kick : k.kick;
-  const T kick_hi = (jb == N && a.bc_hi == kBcReflect) ? -k.kick : k.kick;
+  const T gk_lo = (ja == 0 && a.bc_lo == kBcReflect) ? -k.gk : k.gk;
+  const T gk_hi = (jb == N && a.bc_hi == kBcReflect) ? -k.gk : k.gk;
 
   // March: cell j is updated from the flux on its left face (carried) and
   // the flux on its right face, which needs the face states of cell j+1,
@@ -1883,8 +1883,8 @@ __device__ void colsweep_tile(const SweepArgs<T>& a, const PatchDev& P, int64_t 
     W1 = LDSH ? table_halo(2) : H[2];
   }
   Prim<T> WpPrev, WmC, WpC, dummy;
-  face_states(H[0], H[1], W0, k, kick_lo, dummy, WpPrev);   // cell ja-1
-  face_states(H[1], W0, W1, k, k.kick, WmC, WpC);           // cell ja
+  face_states(H[0], H[1], W0, k, gk_lo, dummy, WpPrev);   // cell ja-1
+  face_states(H[1], W0, W1, k, k.gk, WmC, WpC);           // cell ja
   Cons<T> Fl = hllc(WpPrev, WmC, k);
   WpPrev = WpC;
   std::conditional_t<REG, FaceOut<T>, NoFaces> faces = [&] {
@@ -1896,7 +1896,7 @@ __device__ void colsweep_tile(const SweepArgs<T>& a, const PatchDev& P, int64_t 
   auto advance = [&](const Cons<T>& U2, int j) {
     const Prim<T> W2 = to_prim(U2, k);
     Prim<T> Wm1, Wp1;
-    face_states(W0, W1, W2, k, k.kick, Wm1, Wp1);  // cell j+1
+    face_states(W0, W1, W2, k, k.gk, Wm1, Wp1);  // cell j+1
     const Cons<T> Fr = hllc(WpPrev, Wm1, k);
     faces.put(j, Fl);
     update(U0, Fl, Fr, k);
@@ -1931,18 +1931,23 @@ __device__ void colsweep_tile(const SweepArgs<T>& a, const PatchDev& P, int64_t 
       oa = min(oa + sd, bmax);
       Pq[d] = pl.load(oa);
     }
-    // unrolled 6 times: the carried cells rotate with period 3, the carried
-    // face state and flux with period 2 and the prefetch queue with period
-    // D (a divisor of 6), so the copies vanish
-#pragma unroll 6
-    for (; j < jm; ++j) {
+    auto march = [&] {
       const Cons<T> U2 = Pq[0];
 #pragma unroll
       for (int d = 0; d + 1 < D; ++d) Pq[d] = Pq[d + 1];
       oa = min(oa + sd, bmax);  // cell j+2+D, clamped
       Pq[D - 1] = pl.load(oa);
       advance(U2, j);
+      ++j;
+    };
+    // six at a time: the carried cells rotate with period 3, the carried
+    // face state and flux with period 2 and the prefetch queue with period
+    // D (a divisor of 6), so the copies vanish
+    while (j + 6 <= jm) {
+#pragma unroll
+      for (int u = 0; u < 6; ++u) march();
     }
+    while (j < jm) march();
   }
   if (LDSH) {
     for (; j < jb - 2; ++j) advance(j + 2 == jb - 2 ? E[2] : E[3], j);
@@ -1952,7 +1957,7 @@ __device__ void colsweep_tile(const SweepArgs<T>& a, const PatchDev& P, int64_t 
   for (; j < jb; ++j) {
     const Prim<T> W2 = (j + 2 == jb) ? H[2] : H[3];
     Prim<T> Wm1, Wp1;
-    face_states(W0, W1, W2, k, (j + 1 == jb) ? kick_hi : k.kick, Wm1, Wp1);  // cell j+1
+    face_states(W0, W1, W2, k, (j + 1 == jb) ? gk_hi : k.gk, Wm1, Wp1);  // cell j+1
     const Cons<T> Fr = hllc(WpPrev, Wm1, k);
     faces.put(j, Fl);
     update(U0, Fl, Fr, k);
