@@ -452,6 +452,26 @@ __device__ void tot_block_wide(Acc& t, double vol, double* out, double* red, boo
   t.zero();
 }
 
+// tot_block once per work item for sums held in LDS: after a barrier wave w
+// adds variable v = w, w + nw, ... over the threads in a fixed order (lane l
+// takes t = l, l + 64, ...) straight from their slots, reduces its lanes with
+// wave_sum and scales the result by `vol`: each wave reduces one value in
+// place of six (300 FP64 patches 3.59 -> 3.58 ms a step pair).
+__device__ __forceinline__ void tot_block_item(TotL& t, double vol, double* out, bool grav) {
+  const int B = blockDim.x, nw = (B + 63) >> 6;
+  const int wid = threadIdx.x >> 6, l = threadIdx.x & 63;
+  __syncthreads();
+  for (int v = wid; v < 6; v += nw) {  // wave-uniform
+    const double* q = t.p + (grav || v < 5 ? v : 4);
+    double a = 0.0;
+    for (int j = l; j < B; j += 64) a += q[kTotStride * j];
+    a = wave_sum(a);
+    if (l == 0) out[v] = a * vol;
+  }
+  __syncthreads();
+  t.zero();
+}
+
 template <class T>
 __device__ __forceinline__ Prim<T> shfl_prim(const Prim<T>& W, int src) {
   Prim<T> r;
@@ -842,24 +862,32 @@ __device__ void xsweep_tile(const SweepArgs<T>& a, const PatchDev& P, int64_t ti
   }
 }
 
-// Work item of a persistent launch, made wave-uniform so that the item,
-// the patch record and the plane pointers live in scalar registers.
-__device__ __forceinline__ int next_item(unsigned int* ticket, int* slot) {
-  if (threadIdx.x == 0) *slot = int(atomicAdd(ticket, 1u));
-  __syncthreads();
-  const int it = __builtin_amdgcn_readfirstlane(*slot);
-  __syncthreads();
-  return it;
-}
-
-// The i-th work item of this workgroup: pulled from the ticket (dynamic
-// scheduling), or item blockIdx.x + i gridDim.x (static round robin over the
-// largest-first list: no atomic and no barrier per item).
+// The i-th work item of this workgroup of a persistent launch, made
+// wave-uniform so that the item, the patch record and the plane pointers live
+// in scalar registers: item blockIdx.x first, then items pulled from the
+// ticket (dynamic scheduling) or i gridDim.x further on (static round robin
+// over the largest-first list: no atomic and no barrier per item).  A ticket
+// is drawn one item ahead (`ahead`, held by thread 0), so its trip to memory
+// overlaps the current item; every workgroup draws one past the last.  With no
+// more items than workgroups nothing is drawn.  (The launch caps its grid at
+// the items: 2048 workgroups drawing a ticket each held every sweep of a small
+// batch up by 12 us, and the tuner timed column shapes under that.)  FP64,
+// own dt: 300 patches 3.64 -> 3.57 ms a step pair (with tot_block_item), 16
+// patches 117 -> 101 us a step; one dt: 4 patches 58.4 -> 53.5 us a step; 4096
+// FP32 patches unchanged.
 template <class T>
 __device__ __forceinline__ int item_at(const SweepArgs<T>& a, int i, unsigned int* ticket,
-                                       int* slot) {
-  if (a.dyn) return next_item(ticket, slot);
-  return int(blockIdx.x) + i * int(gridDim.x);
+                                       int* slot, int& ahead) {
+  if (!a.dyn || a.nitems <= int(gridDim.x)) return int(blockIdx.x) + i * int(gridDim.x);
+  int it = int(blockIdx.x);
+  if (i > 0) {
+    if (threadIdx.x == 0) *slot = ahead;
+    __syncthreads();
+    it = __builtin_amdgcn_readfirstlane(*slot);
+    __syncthreads();
+  }
+  if (threadIdx.x == 0) ahead = int(gridDim.x + atomicAdd(ticket, 1u));
+  return it;
 }
 
 // Direct FP32 totals instantiation with whole pencils per wave: four waves per
@@ -892,14 +920,15 @@ __global__ void __launch_bounds__(512, sizeof(T) == 4 && TOT && !MULTI && !PERSI
       tot_block(tot, cell_volume(a.single), a.tpart + 6 * int64_t(blockIdx.x), tred, grav);
     }
   } else {
+    int ahead = 0;
     for (int i = 0;; ++i) {
-      const int it = item_at(a, i, &a.scal->tickets[0], &item_s);
+      const int it = item_at(a, i, &a.scal->tickets[0], &item_s, ahead);
       if (it >= a.nitems) break;
       const WorkItem w = a.items[it];
       const PatchDev P = a.patches[w.patch];
       SweepConst<T> k = make_const<T>(item_dt(a, w.patch, dt), P.dx[0], a.gamma, a.grav);
       xsweep_tile<T, V, MULTI, TOT>(a, P, w.tile, k, slots, smax, bad, tot);
-      if (TOT) tot_block(tot, cell_volume(P), a.tpart + 6 * int64_t(it), tred, grav);
+      if (TOT) tot_block_item(tot, cell_volume(P), a.tpart + 6 * int64_t(it), grav);
       if (MULTI) __syncthreads();
       item_cfl(a, w.patch, smax, red);
     }
@@ -1239,8 +1268,9 @@ __global__ void __launch_bounds__(512, sizeof(T) == 4 && !PERSIST ? 3 : 1)
     if (TOT)
       tot_block(tot, cell_volume(a.single), a.tpart + 6 * int64_t(blockIdx.x), tred, grav);
   } else {
+    int ahead = 0;
     for (int i = 0;; ++i) {
-      const int it = item_at(a, i, &a.scal->tickets[0], &item_s);
+      const int it = item_at(a, i, &a.scal->tickets[0], &item_s, ahead);
       if (it >= a.nitems) break;
       const WorkItem w = a.items[it];
       const PatchDev P = a.patches[w.patch];
@@ -1250,7 +1280,7 @@ __global__ void __launch_bounds__(512, sizeof(T) == 4 && !PERSIST ? 3 : 1)
       const int npen = P.n[1] * P.n[2];
       xmarch_pencils<T, V, TOT>(a, P, w.tile * nw + wave, npen, npen, k, id, lines[wave], smax,
                                 bad, tot);
-      if (TOT) tot_block(tot, cell_volume(P), a.tpart + 6 * int64_t(it), tred, grav);
+      if (TOT) tot_block_item(tot, cell_volume(P), a.tpart + 6 * int64_t(it), grav);
       item_cfl(a, w.patch, smax, red);
     }
   }
@@ -1630,8 +1660,9 @@ __global__ void __launch_bounds__(512) sweep_plane_kernel(SweepArgs<T> a) {
   bool bad = false;
   TotR tot;
   tot.zero();
+  int ahead = 0;
   for (int i = 0;; ++i) {
-    const int it = item_at(a, i, &a.scal->tickets[3], slot);
+    const int it = item_at(a, i, &a.scal->tickets[3], slot, ahead);
     if (it >= a.nitems) break;
     const WorkItem w = a.items[it];
     const PatchDev P = a.patches[w.patch];
@@ -1673,8 +1704,9 @@ __global__ void __launch_bounds__(512) sweep_zplane_kernel(SweepArgs<T> a) {
   bool bad = false;
   TotR tot;
   tot.zero();
+  int ahead = 0;
   for (int i = 0;; ++i) {
-    const int it = item_at(a, i, &a.scal->tickets[2], slot);
+    const int it = item_at(a, i, &a.scal->tickets[2], slot, ahead);
     if (it >= a.nitems) break;
     const WorkItem w = a.items[it];
     const PatchDev P = a.patches[w.patch];
@@ -2003,15 +2035,16 @@ __global__ void __launch_bounds__(512, sizeof(T) == 4 ? (PERSIST && TOT ? 3 : kC
     if (TOT)
       tot_block(tot, cell_volume(a.single), a.tpart + 6 * int64_t(blockIdx.x), tred, grav);
   } else {
+    int ahead = 0;
     for (int i = 0;; ++i) {
-      const int it = item_at(a, i, &a.scal->tickets[AXIS], &item_s);
+      const int it = item_at(a, i, &a.scal->tickets[AXIS], &item_s, ahead);
       if (it >= a.nitems) break;
       const WorkItem w = a.items[it];
       const PatchDev P = a.patches[w.patch];
       SweepConst<T> k = make_const<T>(item_dt(a, w.patch, dt), P.dx[AXIS], a.gamma, a.grav);
       colsweep_tile<T, AXIS, LDSH, TOT, REG>(a, P, w.tile, k, tab, smax, bad, tot, w.patch);
-      __syncthreads();
-      if (TOT) tot_block(tot, cell_volume(P), a.tpart + 6 * int64_t(it), tred, grav);
+      if (!TOT) __syncthreads();  // the halo table is free again
+      if (TOT) tot_block_item(tot, cell_volume(P), a.tpart + 6 * int64_t(it), grav);
       item_cfl(a, w.patch, smax, red);
     }
   }
@@ -2522,6 +2555,11 @@ static hipError_t launch_sweep_t(const LaunchSweep& L, hipStream_t st) {
 }
 
 hipError_t launch_sweep(const LaunchSweep& L, hipStream_t st) {
+  if (L.persistent && L.nitems > 0 && L.nitems < L.nblocks) {
+    LaunchSweep M = L;  // a workgroup per item at most: the others would find none
+    M.nblocks = L.nitems;
+    return launch_sweep(M, st);
+  }
   return L.fp64 ? launch_sweep_t<double>(L, st) : launch_sweep_t<float>(L, st);
 }
 
