@@ -341,32 +341,43 @@ __global__ void __launch_bounds__(kFinalBlock) profile_final_kernel(const double
 // mixed-radix Stockham FFT of fft.hpp (radices 16, 4, 2, 3; output in
 // natural order).  For a real pair packed as a + i b,
 // |A(k)|^2 + |B(k)|^2 = (|Z(k)|^2 + |Z(N-k)|^2) / 2, so the power summed over
-// the components and lines needs no unpacking.  Thread t accumulates k = t,
-// t + 256, ... over its workgroup's lines (fixed order), writes its
-// partial spectrum, and one workgroup sums the partials in a fixed order.
+// the components and lines needs no unpacking: the threads sum |Z(k)|^2 over
+// their lines (each k by 256 / n threads, each over every (256 / n)-th line;
+// or 256 values of k at a time), and the workgroup folds k and N - k once, at
+// its end, into its partial spectrum.  One workgroup a wavenumber sums the
+// partials in a fixed order.
+//
+// Bound by the phases of a pass (loads, FFT stages, sums, with barriers
+// between): two workgroups of 256 threads share a CU's LDS and overlap them,
+// and a pass takes as many lines as fill 4096 complex values, so that a
+// radix-16 stage has a butterfly for nearly every thread.  With one workgroup
+// of 512 threads on a CU, 192 of them in a stage, 129 in the sums, three
+// divisions a cell and the general stages: 256^3 FP32 200 instead of 117 us,
+// FP64 309 instead of 140, 512^3 1830 instead of 1085, 768 x 384 x 768 2350
+// instead of 2140, 64^3 15.7 instead of 12.
 
-// x-lines per pass: the 3/2 complex lines of every x-line of a pass fill at
-// most kSpecElems complex values of LDS
+// the 3/2 complex lines of every x-line of a pass fill at most kSpecElems
+// complex values of LDS
 constexpr int kSpecElems = 4096;
-constexpr int kSpecBlock = 512;  // threads of the spectrum kernel
+constexpr int kSpecBlock = 256;  // threads of the spectrum kernel
 
-template <class T, int P>
-// Short lines (P >= 4) keep their registers (two waves per SIMD); long
-// lines (P = 2) take four waves per SIMD, which measured faster (768^3:
-// 5.5 against 6.7 ms) despite a few spilled registers.
-__global__ void __launch_bounds__(kSpecBlock, P >= 4 ? 2 : 4) spectrum_kernel(DiagArgs<T> a, FftPlan sp) {
+template <class T>
+__global__ void __launch_bounds__(kSpecBlock, 2)
+    spectrum_kernel(DiagArgs<T> a, FftPlan sp, int P, FastDiv dn, FastDiv dny) {
   extern __shared__ double2 sbuf[];
   const PatchDev& Pd = a.single;
-  const int n = sp.n;
+  const int n = sp.n, nl = P + P / 2;
   double2* W = sbuf;       // W[t] = exp(-2 pi i t / n)
   double2* buf = sbuf + n;  // 3P/2 complex lines (fft_pad slots), transformed in place
-  static_assert(P % 2 == 0, "x-lines are paired for their uz lines");
   for (int t = threadIdx.x; t < n; t += kSpecBlock) {
     double sn, cs;
     sincospi(-2.0 * double(t) / double(n), &sn, &cs);
     W[t] = make_double2(cs, sn);
   }
-  constexpr int KPT = (kSpecMaxLen / 2 + 1 + kSpecBlock - 1) / kSpecBlock;  // k per thread
+  // |Z(k)|^2 of k = k0 + 256 i over the lines g, g + ng, ... of every pass
+  constexpr int KPT = (kSpecMaxLen + kSpecBlock - 1) / kSpecBlock;
+  const int ng = n <= kSpecBlock ? kSpecBlock / n : 1;
+  const int g = n <= kSpecBlock ? int(dn.div(threadIdx.x)) : 0, k0 = int(threadIdx.x) - g * n;
   double acc[KPT];
 #pragma unroll
   for (int i = 0; i < KPT; ++i) acc[i] = 0.0;
@@ -376,16 +387,16 @@ __global__ void __launch_bounds__(kSpecBlock, P >= 4 ? 2 : 4) spectrum_kernel(Di
   // this thread's cells c = t + 256 i of the pass (line c / n of the group,
   // x = c mod n), fetched one pass ahead so that the next pass's loads are
   // in flight during the current transform
-  constexpr int XPT = kSpecElems / 2 / kSpecBlock;
+  constexpr int XPT = (kSpecElems * 2 / 3 + kSpecBlock - 1) / kSpecBlock;
   T fr[XPT], fm[XPT][3];
   auto fetch = [&](int grp) {
 #pragma unroll
     for (int i = 0; i < XPT; ++i) {
       const int c = threadIdx.x + i * kSpecBlock;
-      const int lp = c / n;
+      const int lp = int(dn.div(uint32_t(c)));
       const int x = c - lp * n, line = grp * P + lp;
       if (lp < P && line < lines) {
-        const int z = line / ny, y = line - z * ny;
+        const int z = int(dny.div(uint32_t(line))), y = line - z * ny;
         const int64_t o = int64_t(y) * Pd.sy + int64_t(z) * Pd.sz + x;
         fr[i] = p0[o];
 #pragma unroll
@@ -399,49 +410,44 @@ __global__ void __launch_bounds__(kSpecBlock, P >= 4 ? 2 : 4) spectrum_kernel(Di
 #pragma unroll
     for (int i = 0; i < XPT; ++i) {
       const int c = threadIdx.x + i * kSpecBlock;
-      const int lp = c / n;
+      const int lp = int(dn.div(uint32_t(c)));
       const int x = c - lp * n;
       if (lp < P) {
-        double2 z1 = make_double2(0.0, 0.0);  // a missing last line: zeros
-        double uz = 0.0;
-        if (grp * P + lp < lines) {
-          const double r = double(fr[i]);
-          z1 = make_double2(double(fm[i][0]) / r, double(fm[i][1]) / r);
-          uz = double(fm[i][2]) / r;
-        }
-        buf[fft_pad(lp * n + x)] = z1;
+        double u[3] = {0.0, 0.0, 0.0};  // lines past the end: zeros
+        if (grp * P + lp < lines) velocity(fr[i], fm[i], u);
+        buf[fft_pad(lp * n + x)] = make_double2(u[0], u[1]);
         // the real (even lp) or imaginary (odd lp) part of the pair's uz line
         double* zp = reinterpret_cast<double*>(&buf[fft_pad((P + (lp >> 1)) * n + x)]);
-        zp[lp & 1] = uz;
+        zp[lp & 1] = u[2];
       }
     }
     if (grp + int(gridDim.x) < groups) fetch(grp + gridDim.x);
     __syncthreads();
-    fft_lines_inplace<kSpecElems, kSpecBlock>(buf, 3 * P / 2, n, sp, W);
-    // the lines of the pass that hold data: its x-lines, then the uz line of
-    // every pair with at least one x-line (a missing x-line left zeros)
-    const int have = min(P, lines - grp * P);
-    const int nz = (have + 1) >> 1;
+    fft_lines_inplace<kSpecElems, kSpecBlock>(buf, nl, n, sp, W);
 #pragma unroll
-    for (int q = 0; q < P + P / 2; ++q) {
-      if (q < P ? q >= have : q - P >= nz) continue;
-      const int z = q * n;
-#pragma unroll
-      for (int i = 0; i < KPT; ++i) {
-        const int k = threadIdx.x + i * kSpecBlock;
-        if (k <= n / 2) {
-          const int km = k == 0 ? 0 : n - k;
-          const double2 a1 = buf[fft_pad(z + k)], b1 = buf[fft_pad(z + km)];
-          acc[i] += 0.5 * ((a1.x * a1.x + a1.y * a1.y) + (b1.x * b1.x + b1.y * b1.y));
+    for (int i = 0; i < KPT; ++i) {
+      const int k = k0 + i * kSpecBlock;
+      if (k < n && g < ng)
+        for (int q = g; q < nl; q += ng) {
+          const double2 z = buf[fft_pad(q * n + k)];
+          acc[i] += __builtin_fma(z.x, z.x, z.y * z.y);
         }
-      }
     }
   }
-  const int nk = n / 2 + 1;
+  __syncthreads();
+  double* pw = reinterpret_cast<double*>(buf);  // [g][k]
 #pragma unroll
   for (int i = 0; i < KPT; ++i) {
-    const int k = threadIdx.x + i * kSpecBlock;
-    if (k < nk) a.partials[int64_t(blockIdx.x) * nk + k] = acc[i];
+    const int k = k0 + i * kSpecBlock;
+    if (k < n && g < ng) pw[g * n + k] = acc[i];
+  }
+  __syncthreads();
+  const int nk = n / 2 + 1;
+  for (int k = threadIdx.x; k < nk; k += kSpecBlock) {
+    const int km = k == 0 ? 0 : n - k;
+    double s = 0.0;
+    for (int h = 0; h < ng; ++h) s += pw[h * n + k] + pw[h * n + km];
+    a.partials[int64_t(blockIdx.x) * nk + k] = 0.5 * s;
   }
 }
 
@@ -555,26 +561,21 @@ static hipError_t launch_spectrum_t(const LaunchDiag& L, hipStream_t st) {
   const DiagArgs<T> a = to_dargs<T>(L);
   FftPlan sp;
   if (!make_fft_plan(L.single.n[0], sp)) return hipErrorInvalidValue;
-  // x-lines per pass: 8 (an FP64 state: 4, for its prefetch registers) for
-  // lines of up to 256 cells, else 2 (3P/2 n <= kSpecElems)
-  constexpr int PS = sizeof(T) == 8 ? 4 : 8;
+  // x-lines per pass: as many pairs as fill the buffer, but no fewer than 512
+  // groups where there are lines for them (two workgroups per CU)
+  const int n = sp.n;
+  const int64_t nlines = int64_t(L.single.n[1]) * L.single.n[2];
+  const int P = 2 * int(std::max<int64_t>(
+                        1, std::min<int64_t>(kSpecElems / (3 * n), (nlines + 1023) / 1024)));
   // workgroups: about 16 passes each (a workgroup forms the twiddles and ends
-  // in a partial spectrum), 512 to kSpecBlocks of them (L.chunks): 256^3 FP32
-  // 229 -> 197 us against always kSpecBlocks, 64^3 21 -> 16 us; with 512 on
-  // 512^3, 5 % slower
-  const int64_t groups = (int64_t(L.single.n[1]) * L.single.n[2] + (sp.n <= 256 ? PS : 2) - 1) /
-                         (sp.n <= 256 ? PS : 2);
+  // in a partial spectrum), 512 to kSpecBlocks of them (L.chunks)
+  const int64_t groups = (nlines + P - 1) / P;
   const int blocks = int(std::min<int64_t>(std::min<int64_t>(groups, L.chunks),
                                            std::max<int64_t>(512, groups / 16)));
-  if (sp.n <= 256) {
-    const size_t lds = size_t(sp.n + fft_lds(3 * PS / 2 * sp.n)) * sizeof(double2);
-    hipLaunchKernelGGL((spectrum_kernel<T, PS>), dim3(unsigned(blocks)), dim3(kSpecBlock), lds,
-                       st, a, sp);
-  } else {
-    const size_t lds = size_t(sp.n + fft_lds(3 * sp.n)) * sizeof(double2);
-    hipLaunchKernelGGL((spectrum_kernel<T, 2>), dim3(unsigned(blocks)), dim3(kSpecBlock), lds,
-                       st, a, sp);
-  }
+  // (the lines, or at the end kSpecBlock sums)
+  const size_t lds = size_t(n + std::max(fft_lds(3 * P / 2 * n), kSpecBlock / 2)) * sizeof(double2);
+  hipLaunchKernelGGL((spectrum_kernel<T>), dim3(unsigned(blocks)), dim3(kSpecBlock), lds, st, a,
+                     sp, P, FastDiv(uint32_t(n)), FastDiv(uint32_t(L.single.n[1])));
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
   const double lines = double(L.single.n[1]) * L.single.n[2];

@@ -39,16 +39,25 @@
 namespace hydro {
 
 constexpr int kS3Block = 256;
-constexpr int kS3Elems = 4096;  // complex elements of the x pass's lines in LDS
+// complex elements of the x pass's lines in LDS (FP64 cells leave registers for
+// fewer)
+template <class T>
+constexpr int kS3Elems = sizeof(T) == 8 ? 3072 : 4096;
 constexpr int kS3MaxLen = 1024;
 constexpr int kS3ColElems = 4096;  // complex elements of a y or z tile, at most
 constexpr int kS3Pitch = 8;        // kx rows start on multiples of 8 complex values (128 bytes)
 
 // kx columns per tile of a y or z pass over lines of length n: 8, whole
 // 128-byte lines of a row (the z pass strides by a plane: with half lines it
-// took 338 instead of 169 us on 256^3, the y pass 208 instead of 149), where
+// took 338 instead of 169 us on 256^3 (now 152), the y pass 208 instead of
+// 149), where
 // two such tiles share the LDS of a CU, else 4.
 constexpr int s3_cols(int n) { return 8 * n <= kS3ColElems ? 8 : 4; }
+
+// Pitch of the lines of a column tile in LDS: 16 past a multiple of 16 (which
+// lets the FFT stages step linearly; 256 cells: lines 17 x 17 slots apart, so
+// the columns of a row fall on different banks), else one past the length.
+__host__ __device__ constexpr int s3_line(int n) { return n % 16 == 0 ? n + 16 : n + 1; }
 
 struct Spec3Args {
   const void* pool;
@@ -94,10 +103,10 @@ __global__ void __launch_bounds__(kS3Block) spec3_x_kernel(Spec3Args a, FftPlan 
   for (int t = threadIdx.x; t < nx; t += kS3Block) W[t] = a.tw[t];
   const int lines = ny * nz, groups = (lines + G - 1) / G;
   const T* p0 = static_cast<const T*>(a.pool) + a.base0;
-  constexpr int EPT = kS3Elems / 2 / kS3Block;  // x cells per thread and pass
-  for (int grp = blockIdx.x; grp < groups; grp += gridDim.x) {
-    __syncthreads();  // the twiddles, and the previous pass's reads of buf
-    T r[EPT], m[EPT][3];
+  // x cells per thread and pass: a pass's x-lines are 2/3 of its lines
+  constexpr int EPT = (kS3Elems<T> * 2 / 3 + kS3Block - 1) / kS3Block;
+  T r[EPT], m[EPT][3];
+  auto fetch = [&](int grp) {
 #pragma unroll
     for (int i = 0; i < EPT; ++i) {  // every load before any arithmetic
       const int e = threadIdx.x + i * kS3Block;
@@ -110,6 +119,15 @@ __global__ void __launch_bounds__(kS3Block) spec3_x_kernel(Spec3Args a, FftPlan 
         for (int v = 0; v < 3; ++v) m[i][v] = p0[o + (v + 1) * a.plane];
       }
     }
+  };
+  // FP32 cells are fetched a pass ahead, during the current transform: with
+  // the larger passes 256^3 178 -> 151 us, writes of the half spectra included
+  // (146 us at the rate of a large copy); FP64 cells take the registers of it
+  constexpr bool kAhead = sizeof(T) == 4;
+  if (kAhead && int(blockIdx.x) < groups) fetch(blockIdx.x);
+  for (int grp = blockIdx.x; grp < groups; grp += gridDim.x) {
+    __syncthreads();  // the twiddles, and the previous pass's reads of buf
+    if (!kAhead) fetch(grp);
 #pragma unroll
     for (int i = 0; i < EPT; ++i) {
       const int e = threadIdx.x + i * kS3Block;
@@ -118,9 +136,10 @@ __global__ void __launch_bounds__(kS3Block) spec3_x_kernel(Spec3Args a, FftPlan 
         double2 z1 = make_double2(0.0, 0.0);  // lines past the end: zeros
         double uz = 0.0;
         if (line < lines) {
-          const double rho = double(r[i]);
-          z1 = make_double2(double(m[i][0]) / rho, double(m[i][1]) / rho);
-          uz = double(m[i][2]) / rho;
+          double u[3];
+          velocity(r[i], m[i], u);
+          z1 = make_double2(u[0], u[1]);
+          uz = u[2];
         }
         buf[fft_pad(lp * nx + x)] = z1;
         // uz of x-lines 2q and 2q + 1 as the real and imaginary parts of
@@ -130,8 +149,9 @@ __global__ void __launch_bounds__(kS3Block) spec3_x_kernel(Spec3Args a, FftPlan 
         if ((G & 1) && lp == G - 1) zp[1] = 0.0;
       }
     }
+    if (kAhead && grp + int(gridDim.x) < groups) fetch(grp + gridDim.x);
     __syncthreads();
-    fft_lines_inplace<kS3Elems, kS3Block>(buf, G + (G + 1) / 2, nx, px, W);
+    fft_lines_inplace<kS3Elems<T>, kS3Block>(buf, G + (G + 1) / 2, nx, px, W);
     // Z = X + i Y with X, Y the DFTs of two real lines (ux and uy of an
     // x-line, or uz of two x-lines):
     // X(k) = (Z(k) + conj Z(n-k)) / 2, Y(k) = -i (Z(k) - conj Z(n-k)) / 2
@@ -160,7 +180,7 @@ __global__ void __launch_bounds__(kS3Block) spec3_x_kernel(Spec3Args a, FftPlan 
 template <bool ZP, int E>
 __global__ void __launch_bounds__(kS3Block) spec3_col_kernel(Spec3Args a, FftPlan pl) {
   extern __shared__ double2 s3lds[];
-  const int nx = a.n[0], ny = a.n[1], nz = a.n[2], nh = a.nh, np = a.np, L = pl.n, ls = L + 1;
+  const int nx = a.n[0], ny = a.n[1], nz = a.n[2], nh = a.nh, np = a.np, L = pl.n, ls = s3_line(L);
   const int T = s3_cols(L), lt = T == 8 ? 3 : 2, ntk = (nh + T - 1) >> lt;
   double2* W = s3lds;
   double2* buf = s3lds + L;
@@ -232,7 +252,7 @@ template <bool ZP>
 static void launch_s3_cols(const Spec3Args& a, const FftPlan& pl, hipStream_t st) {
   const int T = s3_cols(pl.n), ntk = (a.nh + T - 1) / T;
   const dim3 grid(unsigned((ZP ? a.n[1] : 3 * a.n[2]) * ntk));
-  const size_t lds = size_t(pl.n + fft_lds(T * (pl.n + 1))) * sizeof(double2);
+  const size_t lds = size_t(pl.n + fft_lds(T * s3_line(pl.n))) * sizeof(double2);
   if (T * pl.n <= 2048)
     hipLaunchKernelGGL((spec3_col_kernel<ZP, 2048>), grid, dim3(kS3Block), lds, st, a, pl);
   else
@@ -349,7 +369,12 @@ static hipError_t launch_s3(const LaunchSpec3& L, hipStream_t st) {
   for (int i = 0; i < 3; ++i) a.n[i] = P.n[i];
   a.nh = P.n[0] / 2 + 1;
   a.np = s3_pitch(P.n[0]);
-  a.gx = std::max(1, (kS3Elems / 2) / P.n[0]);
+  // as many x-lines, with their uz lines, as the pass's buffer holds, but no
+  // fewer than 512 passes where there are lines for them
+  const int64_t nlines = int64_t(P.n[1]) * P.n[2];
+  a.gx = 1;
+  while ((a.gx + 1 + (a.gx + 2) / 2) * P.n[0] <= kS3Elems<T> && 512 * int64_t(a.gx) < nlines)
+    ++a.gx;
   a.nb = shell_count_host(P.n);
   a.cplane = int64_t(a.np) * P.n[1] * P.n[2];
   char* w = static_cast<char*>(L.work);
