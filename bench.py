@@ -10,7 +10,7 @@ reflecting z walls), `batch` (4096 uneven periodic KH patches, one
 persistent launch per sweep).  A zone-update is one interior zone advanced
 one full step: three sweeps, the fused CFL reduction that sets the next dt
 and the fused FP64 conserved totals.  The state is resident in HBM before
-the timed region starts; the timed steps are graph replays bracketed by
+the timed region starts; the timed steps are direct launches bracketed by
 device synchronisation.
 
 Prints ONE JSON line.  Fields beyond the driver's contract:
@@ -86,7 +86,7 @@ WORKLOADS = {
     "batch": "4096 independent periodic KH patches, edges from {16,32,48,64} (seeded), "
              "4 stored ghost layers, rows padded so each interior row starts on a 128-byte "
              "boundary, gamma 5/3, shear 0.1-1.0, density ratio 1-4; one persistent launch "
-             "per sweep, hipGraph step, one global dt",
+             "per sweep, one global dt",
 }
 
 
@@ -506,7 +506,7 @@ def shell_spectrum_timing(obj, W, zones, timed, torch):
 
 def per_patch_loop(W, prec, npatch, steps, torch, hydro):
     """The batch's first `npatch` patches stepped one by one, each as its own
-    grid (hydro_step, one graph launch per patch per step): the baseline that
+    grid (hydro_step, its own launches per patch and step): the baseline that
     the single persistent launch per sweep replaces.  Returns zone-updates/s."""
     import numpy as np
     import hydro_ic as ic
@@ -516,7 +516,7 @@ def per_patch_loop(W, prec, npatch, steps, torch, hydro):
         U = torch.from_numpy(ic.kh_patch(s).astype(dtype)).to("cuda:0")
         grids.append(hydro.Grid(U, 1.0 / s.n, 5.0 / 3.0, flags=hydro.FLAG_NO_TUNE))
         zones += s.n ** 3
-    for g in grids:          # warm-up step (first-step CFL, graph upload)
+    for g in grids:          # warm-up step (first-step CFL)
         g.step()
     torch.cuda.synchronize()
     t0 = time.perf_counter()
@@ -941,7 +941,7 @@ def main():
         l64 = per_patch_loop(W, hydro.FP64, npl, 5, torch, hydro)
         out["per_patch_loop"] = {
             "sample": f"the first {npl} patches, each its own grid stepped by hydro_step "
-                      "(one graph launch per patch per step), 5 timed steps",
+                      "(its own launches per patch and step), 5 timed steps",
             "fp32": l32, "fp64": l64, "unit": "zone-updates/s",
             "batch_fp32_over_loop_fp32": value / l32,
             "batch_fp32_over_loop_fp64": value / l64}

@@ -1373,9 +1373,9 @@ __device__ __forceinline__ void row_run_off(const RowBases<T>& B, uint32_t off,
 
 // Where the pencils of a plane sweep live in memory, as the plane functions
 // below see them: a rectangle of n(0) x n(1) cells of one plane whose part
-// [lo(0), hi(0)) x [lo(1), hi(1)) is written.  at(base, x, y) is cell (x, y)
-// of variable 0 in a buffer laid out like the state; cell(x, y) gives its
-// grid coordinates (totals).
+// [lo(0), hi(0)) x [lo(1), hi(1)) is written.  off(x, y) is the byte offset of
+// cell (x, y) from the plane bases of a buffer laid out like the state;
+// cell(x, y) gives its grid coordinates (totals).
 //  * PatchPlane: the whole z-plane of a batch patch, read and written in
 //    place, with the launch's boundary conditions at the pencil ends.
 //  * PatchZPlane: an x-z plane of a batch patch (below).
@@ -1395,10 +1395,6 @@ struct PatchPlane {
   __device__ int3 cell(int x, int y) const { return make_int3(x, y, z); }
   __device__ T* src() const { return a.pool; }
   __device__ T* dst() const { return a.pool; }
-  __device__ int64_t plane() const { return P.plane; }
-  __device__ T* at(T* base, int x, int y) const {
-    return base + P.base0 + int64_t(z) * P.sz + int64_t(y) * P.sy + x;
-  }
   __device__ RowBases<T> bases(T* buf) const { return row_bases(buf, P.base0, P.plane); }
   __device__ uint32_t off(int x, int y) const {
     return uint32_t(z * P.sz + y * P.sy + x) * uint32_t(sizeof(T));
@@ -1421,10 +1417,6 @@ struct PatchZPlane {
   __device__ int3 cell(int x, int y) const { return make_int3(x, yr, y); }
   __device__ T* src() const { return a.pool; }
   __device__ T* dst() const { return a.pool; }
-  __device__ int64_t plane() const { return P.plane; }
-  __device__ T* at(T* base, int x, int y) const {
-    return base + P.base0 + int64_t(y) * P.sz + int64_t(yr) * P.sy + x;
-  }
   __device__ RowBases<T> bases(T* buf) const { return row_bases(buf, P.base0, P.plane); }
   __device__ uint32_t off(int x, int y) const {
     return uint32_t(y * P.sz + yr * P.sy + x) * uint32_t(sizeof(T));
@@ -1448,54 +1440,11 @@ struct WindowPlane {
   __device__ int3 cell(int x, int y) const { return make_int3(gx(x), gy(y), z); }
   __device__ T* src() const { return a.pool; }
   __device__ T* dst() const { return a.dst; }
-  __device__ int64_t plane() const { return G.plane; }
-  __device__ T* at(T* base, int x, int y) const {
-    return base + G.base0 + int64_t(z) * G.sz + int64_t(gy(y)) * G.sy + gx(x);
-  }
   __device__ RowBases<T> bases(T* buf) const { return row_bases(buf, G.base0, G.plane); }
   __device__ uint32_t off(int x, int y) const {
     return uint32_t(z * G.sz + gy(y) * G.sy + gx(x)) * uint32_t(sizeof(T));
   }
 };
-
-// The plane between memory and LDS (LOAD: every cell from m.src(), else the
-// written part to m.dst()).  LDS row r holds variable r mod 5 of y = r / 5.
-template <class T, int V, bool LOAD, class M>
-__device__ void plane_copy(const M& m, T* lds) {
-  const int nx = m.n(0), ny = m.n(1);
-  const int nq = nx / V;    // runs per row (<= 64)
-  const int rpw = 64 / nq;  // rows per wave
-  const int l = threadIdx.x & 63, wave = threadIdx.x >> 6, nw = blockDim.x >> 6;
-  const int r = l / nq, q = l - r * nq;
-  if (r >= rpw) return;
-  const int64_t pl = m.plane();
-  const int step = nw * rpw;
-  auto laddr = [&](int row) { return lds + row * kPlanePitch + plane_col<V>(q * V, row / 5); };
-  if (LOAD) {
-    T* base = m.src();
-    const int rows = 5 * ny;
-    // B runs in flight per lane before the first LDS write
-    constexpr int B = int(128 / (V * sizeof(T))) < 8 ? int(128 / (V * sizeof(T))) : 8;
-    for (int row0 = wave * rpw + r; row0 < rows; row0 += B * step) {
-      T buf[B][V];
-#pragma unroll
-      for (int b = 0; b < B; ++b) {
-        const int row = row0 + b * step, y = row / 5;
-        if (row < rows) copy_run<T, V>(buf[b], m.at(base, q * V, y) + int64_t(row - 5 * y) * pl);
-      }
-#pragma unroll
-      for (int b = 0; b < B; ++b)
-        if (row0 + b * step < rows) copy_run<T, V>(laddr(row0 + b * step), buf[b]);
-    }
-  } else {
-    T* base = m.dst();
-    if (q * V < m.lo(0) || q * V >= m.hi(0)) return;
-    for (int row = 5 * m.lo(1) + wave * rpw + r; row < 5 * m.hi(1); row += step) {
-      const int y = row / 5;
-      copy_run<T, V>(m.at(base, q * V, y) + int64_t(row - 5 * y) * pl, laddr(row));
-    }
-  }
-}
 
 // Reads (write = false) or writes the V cells of a run in LDS: the cells at
 // (x0 + c dx, y0 + c dy), c < V, of the five variables, rotated into the
@@ -1516,6 +1465,46 @@ __device__ __forceinline__ void plane_run(T* lds, int x0, int y0, Cons<T> (&U)[V
       p[4 * P] = U[c].e;
     } else {
       U[c] = Cons<T>{p[0], p[vn * P], p[vt1 * P], p[vt2 * P], p[4 * P]};
+    }
+  }
+}
+
+// The plane between memory and LDS (LOAD: every cell from m.src(), else the
+// written part to m.dst()), a row run of all five variables at a time: one
+// byte offset in memory and one LDS address serve the five.  Run by run of
+// one variable, with a 64-bit address and a division by 5 each, the copy was
+// about 65 of the 405 VALU instructions a zone of a window launch, which issue
+// bounds: a step pair of 768^3 FP32 zones 19.5 instead of 18.9 ms, of 4096
+// FP32 patches 18.95 instead of 18.43 ms.
+template <class T, int V, bool LOAD, class M>
+__device__ void plane_copy(const M& m, T* lds) {
+  const int nx = m.n(0), ny = m.n(1);
+  const int nq = nx / V;    // runs per row (<= 64)
+  const int rpw = 64 / nq;  // rows per wave
+  const int l = threadIdx.x & 63, wave = threadIdx.x >> 6, nw = blockDim.x >> 6;
+  const int r = l / nq, x = (l - r * nq) * V;
+  if (r >= rpw) return;
+  const int step = nw * rpw;
+  if (LOAD) {
+    const RowBases<T> sb = m.bases(m.src());
+    // B rows in flight per lane before the first LDS write
+    constexpr int B = V * sizeof(T) <= 8 ? 2 : 1;
+    for (int y0 = wave * rpw + r; y0 < ny; y0 += B * step) {
+      Cons<T> U[B][V];
+#pragma unroll
+      for (int b = 0; b < B; ++b)
+        if (y0 + b * step < ny) row_run_off<T, V, false>(sb, m.off(x, y0 + b * step), U[b]);
+#pragma unroll
+      for (int b = 0; b < B; ++b)
+        if (y0 + b * step < ny) plane_run<T, V, 0, true>(lds, x, y0 + b * step, U[b]);
+    }
+  } else {
+    if (x < m.lo(0) || x >= m.hi(0)) return;
+    const RowBases<T> db = m.bases(m.dst());
+    for (int y = m.lo(1) + wave * rpw + r; y < m.hi(1); y += step) {
+      Cons<T> U[V];
+      plane_run<T, V, 0, false>(lds, x, y, U);
+      row_run_off<T, V, true>(db, m.off(x, y), U);
     }
   }
 }
