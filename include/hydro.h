@@ -355,7 +355,8 @@ int hydro_diag_spectrum(hydro_ctx* c, double* out);
  * (Parseval).  Every extent must be 2^a 3^b with 1 <= n <= 1024
  * (HYDRO_EINVAL otherwise).  `work` is a caller-owned DEVICE buffer of at
  * least the bytes hydro_diag_spectrum3d_workspace_bytes reports (256-byte
- * aligned; about 28 bytes per cell: the three half spectra, their power and
+ * aligned; 28 bytes per cell and up, rows of nx / 2 + 1 values being padded to
+ * multiples of 8: the three half spectra, their power and
  * the partial spectra); its contents are overwritten and need not be kept
  * between calls.  Sums run in a fixed order: bitwise reproducible for a
  * shape.  Asynchronous on the context's stream (the state and `work` must

@@ -78,10 +78,19 @@ __device__ __forceinline__ void all_substeps(int nsub, First first, Next next) {
 // it stands.
 constexpr int kScaledSubsteps = 8;
 
+// 1 / x: the estimate after two Newton steps whose residuals are exact is
+// rounded as the quotient is, in half the instructions of a division (the same
+// bits in every burn measured);
+// div_fixup keeps 0, infinity and NaN as a division has them.
+__device__ __forceinline__ double recip(double x) {
+  return __builtin_amdgcn_div_fixup(rcp(x), x, 1.0);
+}
+
 // The kernel is bound by FP64 issue.  13 species and 64 substeps on 256^3
 // FP32 zones: with (X_s + c_s X_{s-1}) d_s as three operations, a division
 // per link for Ta / T and the network's constants hoisted out of a
-// grid-stride loop into spilled scalars 1.72 ms; now 0.98 ms (held to 128 registers it spills: 1.32 ms).
+// grid-stride loop into spilled scalars 1.72 ms; with divisions 1 / (1 + h k)
+// 0.974 ms; now 0.950 ms (held to 128 registers it spills: 1.32 ms).
 template <class T, int M>
 __global__ void __launch_bounds__(kBurnBlock) burn_kernel(BurnArgs<T> a) {
   const PatchDev& P = a.single;
@@ -116,7 +125,7 @@ __global__ void __launch_bounds__(kBurnBlock) burn_kernel(BurnArgs<T> a) {
 #pragma unroll
   for (int s = 0; s < M; ++s) {
     const double hk = s < M - 1 ? a.h * (a.A[s] * exp(-over_temp(a.Ta[s]))) : 0.0;
-    d[s] = s < M - 1 ? 1.0 / (1.0 + hk) : 1.0;
+    d[s] = s < M - 1 ? recip(1.0 + hk) : 1.0;
     if (s + 1 < M) c[s + 1] = hk;
   }
   bool scaled = a.nsub >= kScaledSubsteps;
