@@ -294,13 +294,14 @@ __device__ __forceinline__ void link_block(int& link, unsigned& bx) {
 template <class T, bool COLD, bool PAIR, bool ODD>
 __device__ void prolong_link(const AmrArgs<T>& a, const AmrLink& L, const PatchDev& F,
                              const PatchDev& C, unsigned bx) {
-  const int g = a.ghosts_only ? F.ng : 0;
+  const bool shell = a.ghosts_only != 0;  // without stored ghosts: no cells
+  const int g = shell ? F.ng : 0;
   const int h = (g + 1) >> 1;  // parents beyond the interior's on each side
   const unsigned ix = unsigned(F.n[0]) >> 1, iy = unsigned(F.n[1]) >> 1,
                  iz = unsigned(F.n[2]) >> 1;  // the interior's parents
   const unsigned o = 2u * unsigned(h), px = ix + o, py = iy + o;
   const unsigned zpart = o * py * px, ypart = iz * o * px;
-  const unsigned total = g ? zpart + ypart + iz * iy * o : iz * iy * ix;
+  const unsigned total = shell ? zpart + ypart + iz * iy * o : iz * iy * ix;
   // t-th parent outside [0, I) along an axis: -h .. -1, then I ..
   auto outside = [&](unsigned t, unsigned I) {
     return int(t) < h ? int(t) - h : int(I) + int(t) - h;
@@ -321,7 +322,7 @@ __device__ void prolong_link(const AmrArgs<T>& a, const AmrLink& L, const PatchD
   const double th = a.theta;
   for (unsigned c = bx * kAmrBlock + threadIdx.x; c < total; c += gridDim.x * kAmrBlock) {
     int pi, pj, pk;
-    if (!g) {
+    if (!shell) {
       const unsigned row = c / ix, kk = row / iy;
       pi = int(c - row * ix);
       pj = int(row - kk * iy);

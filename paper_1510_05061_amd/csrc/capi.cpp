@@ -2059,14 +2059,15 @@ int check_link(const hydro_ctx* c, const hydro_amr_link& k, bool prolong, bool g
 }
 
 // Coarse parents that a prolongation walks for a fine patch of interior
-// extents n (even): the interior's (g = 0), or those of its g ghost layers.
-int64_t prolong_parents(const int64_t n[3], int64_t g) {
+// extents n (even) and g ghost layers: the interior's, or those of the ghost
+// layers alone (none where g = 0).
+int64_t prolong_parents(const int64_t n[3], int64_t g, bool ghosts_only) {
   int64_t box = 1, inner = 1;
   for (int a = 0; a < 3; ++a) {
     box *= n[a] / 2 + 2 * ((g + 1) / 2);
     inner *= n[a] / 2;
   }
-  return g > 0 ? box - inner : inner;
+  return ghosts_only ? box - inner : inner;
 }
 
 int amr_links(hydro_ctx* c, const hydro_amr_link* links, int32_t n, int op, int ghosts_only) {
@@ -2095,9 +2096,10 @@ int amr_links(hydro_ctx* c, const hydro_amr_link* links, int32_t n, int op, int 
         most = std::max(most, int64_t(F.n[0] / 2) * (F.n[1] / 2) * (F.n[2] / 2));
       } else {
         const int64_t nf[3] = {F.n[0], F.n[1], F.n[2]};
-        most = std::max(most, prolong_parents(nf, ghosts_only ? F.ng : 0));
+        most = std::max(most, prolong_parents(nf, F.ng, ghosts_only != 0));
       }
     }
+    if (most == 0) continue;  // ghost layers of patches that store none
     L.cells = most;
     HIP_TRY(launch_amr(L, c->stream));
   }
@@ -2224,7 +2226,7 @@ int level_launch(const hydro_ctx* coarse, const hydro_ctx* fine, const hydro_amr
     } else if (op == kAmrSnapshot) {
       cells = (nf[0] / 2 + 2 * mg) * (nf[1] / 2 + 2 * mg) * (nf[2] / 2 + 2 * mg);
     } else if (op == kAmrProlong) {
-      cells = prolong_parents(nf, g);  // the level step fills ghosts only
+      cells = prolong_parents(nf, g, true);  // the level step fills ghosts only
     } else {
       cells = std::max({nf[1] * nf[2], nf[0] * nf[2], nf[0] * nf[1]}) / 4;
     }
