@@ -90,7 +90,8 @@ __device__ __forceinline__ double recip(double x) {
 // FP32 zones: with (X_s + c_s X_{s-1}) d_s as three operations, a division
 // per link for Ta / T and the network's constants hoisted out of a
 // grid-stride loop into spilled scalars 1.72 ms; with divisions 1 / (1 + h k)
-// 0.974 ms; now 0.950 ms (held to 128 registers it spills: 1.32 ms).
+// 0.974 ms; without 0.950 ms (held to 128 registers it spills: 1.32 ms); with a
+// branch for an exponent out of range in place of a select 0.935 -> 0.910 ms.
 template <class T, int M>
 __global__ void __launch_bounds__(kBurnBlock) burn_kernel(BurnArgs<T> a) {
   const PatchDev& P = a.single;
@@ -111,12 +112,12 @@ __global__ void __launch_bounds__(kBurnBlock) burn_kernel(BurnArgs<T> a) {
   const double temp = ((a.gamma - 1.0) * (e - (0.5 * m2) / r)) / r;
   // Ta / T for every link from one reciprocal: the residual of the product
   // corrects it to the quotient (a rounding error of the exponent would be
-  // carried through all substeps); at T = 0 the product is the quotient
+  // carried through all substeps).  Where the product or 1 / T overflows, or T
+  // is no finite number, the correction is NaN and the quotient is divided out.
   const double itemp = 1.0 / temp;
-  const bool finite = fabs(itemp) < __builtin_huge_val();
   auto over_temp = [&](double ta) {
-    const double q = ta * itemp;
-    return finite ? fma(fma(-q, temp, ta), itemp, q) : q;
+    const double q = ta * itemp, c = fma(fma(-q, temp, ta), itemp, q);
+    return __builtin_expect(c == c, 1) ? c : ta / temp;
   };
   double e0 = 0.0;
 #pragma unroll
