@@ -73,9 +73,9 @@ __device__ __forceinline__ void all_substeps(int nsub, First first, Next next) {
 // X_s <- d_s X_s + e_s X_{s-1} becomes W_s <- d_s W_s + W_{s-1}, one FMA (and
 // one rounding) per species and substep instead of two.  The scaling costs
 // about 14 instructions per species, two an update are saved: it pays from
-// seven substeps on.  A zone whose a_s leave [2^-400, 2^64] (a frozen link;
-// the bounds keep W within range and X / a_s from underflow) is stepped as
-// it stands.
+// seven substeps on.  A zone whose a_s leave [2^-400, 2^64] (a frozen link) or,
+// in FP64, with a species above 2^600 is stepped as it stands: the bounds keep W
+// within range and X / a_s from underflow.
 constexpr int kScaledSubsteps = 8;
 
 // 1 / x: the estimate after two Newton steps whose residuals are exact is
@@ -136,7 +136,9 @@ __global__ void __launch_bounds__(kBurnBlock) burn_kernel(BurnArgs<T> a) {
     for (int s = 1; s < M; ++s) {
       g *= c[s] * d[s];
       scaled = scaled && g >= 0x1p-400 && g <= 0x1p64;
+      if (sizeof(T) == 8) scaled = scaled && fabs(X[s]) <= 0x1p600;
     }
+    if (sizeof(T) == 8) scaled = scaled && fabs(X[0]) <= 0x1p600;
   }
   if (scaled) {
     double g = 1.0;
