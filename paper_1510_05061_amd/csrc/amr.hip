@@ -308,12 +308,14 @@ __device__ void prolong_link(const AmrArgs<T>& a, const AmrLink& L, const PatchD
   };
   // wave-uniform bases and one 32-bit byte offset per cell (a plane is below
   // 4 GiB): the coarse base is the lowest neighbour of the lowest parent, the
-  // fine base its first child
+  // fine base the first cell written.  With an odd number of layers the lowest
+  // parents' first children lie before it: their offsets wrap, and those of the
+  // cells that are written come out right modulo 2^32
   const int64_t corner = C.base0 + (L.ox - h - 1) + int64_t(L.oy - h - 1) * C.sy +
                          int64_t(L.oz - h - 1) * C.sz;
   const T* c0 = a.pool + corner;
   const T* o0 = COLD ? a.cold + corner : nullptr;
-  T* f0 = a.fpool + F.base0 - 2 * h * (1 + int64_t(F.sy) + int64_t(F.sz));
+  T* f0 = a.fpool + F.base0 - g * (1 + int64_t(F.sy) + int64_t(F.sz));
   const unsigned csy = unsigned(C.sy) * sizeof(T), csz = unsigned(C.sz) * sizeof(T);
   const unsigned fsy = unsigned(F.sy) * sizeof(T), fsz = unsigned(F.sz) * sizeof(T);
   auto at = [](const T* p, unsigned b) {
@@ -345,8 +347,8 @@ __device__ void prolong_link(const AmrArgs<T>& a, const AmrLink& L, const PatchD
     }
     const unsigned pc = unsigned(pi + h + 1) * unsigned(sizeof(T)) + unsigned(pj + h + 1) * csy +
                         unsigned(pk + h + 1) * csz;
-    const unsigned fc = 2 * (unsigned(pi + h) * unsigned(sizeof(T)) + unsigned(pj + h) * fsy +
-                             unsigned(pk + h) * fsz);
+    const unsigned fc = unsigned(2 * pi + g) * unsigned(sizeof(T)) + unsigned(2 * pj + g) * fsy +
+                        unsigned(2 * pk + g) * fsz;
     double u[5][7];
 #pragma unroll
     for (int v = 0; v < 5; ++v) {
@@ -381,14 +383,15 @@ __device__ void prolong_link(const AmrArgs<T>& a, const AmrLink& L, const PatchD
       for (int r = 0; r < 4; ++r) {
         const double oy = (r & 1) ? 0.25 : -0.25, oz = (r >> 1) ? 0.25 : -0.25;
         const T y0 = T((x0 + oy * dy) + oz * dz), y1 = T((x1 + oy * dy) + oz * dz);
-        T* f = const_cast<T*>(at(fv, fc + (r & 1) * fsy + (r >> 1) * fsz));
+        const unsigned fr = fc + (r & 1) * fsy + (r >> 1) * fsz;
+        auto cell = [&](unsigned b) { return const_cast<T*>(at(fv, b)); };
         if (!ODD) {
-          store_pair<PAIR>(f, y0, y1);
+          store_pair<PAIR>(cell(fr), y0, y1);
         } else {
           const int i = 2 * pi, j = 2 * pj + (r & 1), k = 2 * pk + (r >> 1);
           if (j < -g || j >= F.n[1] + g || k < -g || k >= F.n[2] + g) continue;
-          if (i >= -g) f[0] = y0;
-          if (i + 1 < F.n[0] + g) f[1] = y1;
+          if (i >= -g) *cell(fr) = y0;
+          if (i + 1 < F.n[0] + g) *cell(fr + unsigned(sizeof(T))) = y1;
         }
       }
     }
