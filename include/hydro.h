@@ -353,12 +353,13 @@ int hydro_diag_spectrum(hydro_ctx* c, double* out);
  * K = 0 .. nshells - 1, where nshells - 1 is the shell of the corner
  * wavevector (nx/2, ny/2, nz/2) (integer halves); sum_K out[K] = <|u|^2>/2
  * (Parseval).  Every extent must be 2^a 3^b with 1 <= n <= 1024
- * (HYDRO_EINVAL otherwise).  `work` is a caller-owned DEVICE buffer of at
- * least the bytes hydro_diag_spectrum3d_workspace_bytes reports (256-byte
- * aligned; 28 bytes per cell and up, rows of nx / 2 + 1 values being padded to
- * multiples of 8: the three half spectra, their power and
- * the partial spectra); its contents are overwritten and need not be kept
- * between calls.  Sums run in a fixed order: bitwise reproducible for a
+ * (HYDRO_EINVAL otherwise).  `work` is a caller-owned DEVICE buffer
+ * (256-byte aligned) of the bytes that hydro_diag_spectrum3d_workspace_bytes
+ * reports: the three half spectra, their power and the partial spectra, about
+ * 28 bytes per cell, with rows of nx / 2 + 1 values padded to multiples of 8
+ * where nx >= 128.  A buffer without room for that padding is taken too (the
+ * same bits, slower); a smaller one is HYDRO_EINVAL.  Its contents are
+ * overwritten and need not be kept between calls.  Sums run in a fixed order: bitwise reproducible for a
  * shape.  Asynchronous on the context's stream (the state and `work` must
  * stay valid until it completes).  Errors: HYDRO_EINVAL, HYDRO_ESTATE
  * (batch context), HYDRO_EDEVICE. */

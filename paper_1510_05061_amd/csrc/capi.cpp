@@ -1952,7 +1952,7 @@ int hydro_diag_spectrum3d(hydro_ctx* c, void* work, size_t work_bytes, double* o
   if (reinterpret_cast<uintptr_t>(out) & 7) return fail(HYDRO_EINVAL, "out must be 8-byte aligned");
   if (reinterpret_cast<uintptr_t>(work) & 255)
     return fail(HYDRO_EINVAL, "the workspace must be 256-byte aligned");
-  if (work_bytes < spec3_workspace_bytes(c->single, nullptr))
+  if (work_bytes < spec3_least_bytes(c->single))
     return fail(HYDRO_EINVAL, "workspace too small (hydro_diag_spectrum3d_workspace_bytes)");
   LaunchSpec3 L{};
   L.pool = c->pool;
@@ -1960,6 +1960,7 @@ int hydro_diag_spectrum3d(hydro_ctx* c, void* work, size_t work_bytes, double* o
   L.fp64 = c->fp64;
   L.cu_count = c->cu_count;
   L.work = work;
+  L.work_bytes = work_bytes;
   L.out = out;
   HIP_TRY(launch_diag_spectrum3d(L, c->stream));
   return HYDRO_OK;

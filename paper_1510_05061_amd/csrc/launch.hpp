@@ -224,13 +224,16 @@ struct LaunchSpec3 {
   PatchDev single;
   int32_t fp64;
   int32_t cu_count;
-  void* work;   // spec3_workspace_bytes(single) bytes, 256-byte aligned
+  void* work;   // 256-byte aligned
+  size_t work_bytes;  // spec3_least_bytes(single) or more
   double* out;  // device, one value per shell
 };
 // every extent 2^a 3^b, from 1 to 1024
 bool spec3_shape_ok(const PatchDev& P);
-// workspace bytes; *nb receives the number of shells
+// workspace bytes (*nb receives the number of shells), and the least that
+// will do, with rows back to back: the same bits
 size_t spec3_workspace_bytes(const PatchDev& P, int* nb);
+size_t spec3_least_bytes(const PatchDev& P);
 hipError_t launch_diag_spectrum3d(const LaunchSpec3& L, hipStream_t st);
 hipError_t launch_cfl(const LaunchReduce& L, hipStream_t st);
 hipError_t launch_totals(const LaunchReduce& L, hipStream_t st);
