@@ -475,8 +475,10 @@ int hydro_amr_prolong(hydro_ctx* c, const hydro_amr_link* links, int32_t n, int 
  * recomputed before its next HYDRO_DT_CFL step.  The workspace (256-byte
  * aligned, hydro_amr_step_workspace_bytes) holds the start-of-step copy of
  * the coarse cells that prolongation reads (at the coarse pool's offsets, so
- * it is as large as the pool), the registers, the fluxes of one fine substep
- * through the fine patches' faces and the link table.  Asynchronous.  Errors:
+ * it is as large as the pool), the registers, the link table and, where the
+ * fine batch's configuration fuses x and y (f=1), the fluxes of one fine
+ * substep through the fine patches' faces.  A workspace without room for those
+ * fluxes is taken too (the same bits, slower).  Asynchronous.  Errors:
  * HYDRO_EINVAL, HYDRO_ESTATE (not batches, work lists out of date),
  * HYDRO_EDEVICE. */
 #define HYDRO_AMR_NO_REFLUX 0x1u

@@ -2240,33 +2240,38 @@ int level_launch(const hydro_ctx* coarse, const hydro_ctx* fine, const hydro_amr
 }
 
 // The workspace of a level step: the start-of-step copy of the coarse cells,
-// the registers (coarse, then fine), the fine face fluxes of a substep and
-// the link table.
+// the registers (coarse, then fine), the link table and, where the fine batch
+// fuses x and y per patch plane, the fine face fluxes of a substep.  A
+// workspace that ends after the link table will do: the step then takes the
+// register launches, with the same bits.
 struct LevelLayout {
   int64_t maxface, nreg;
-  size_t reg, face, links, total;  // byte offsets
+  size_t reg, links, face;  // byte offsets
+  size_t least, total;      // bytes without and with the face fluxes
 };
+bool level_fused(const hydro_ctx* fine) { return fine->cfg.batch_fuse && plane_ok(fine, fine->cfg); }
 LevelLayout level_layout(const hydro_ctx* coarse, const hydro_ctx* fine, int g) {
   LevelLayout l;
   l.maxface = level_maxface(fine, g);
   l.nreg = int64_t(fine->npatch) * 30 * l.maxface;
   l.reg = align256(coarse->pool_bytes);
-  l.face = l.reg + align256(size_t(2 * l.nreg) * sizeof(double));
-  l.links = l.face + align256(size_t(4 * l.nreg) * (fine->fp64 ? 8 : 4));
-  l.total = l.links + size_t(fine->npatch) * sizeof(AmrLink);
+  l.links = l.reg + align256(size_t(2 * l.nreg) * sizeof(double));
+  l.least = l.links + size_t(fine->npatch) * sizeof(AmrLink);
+  l.face = align256(l.least);
+  l.total = level_fused(fine) ? l.face + size_t(4 * l.nreg) * (fine->fp64 ? 8 : 4) : l.least;
   return l;
 }
 
 // The sweeps of one step of a level, each preceded by the flux registers of
 // its axis; then the step bookkeeping.  Where the fine batch fuses x and y
-// per patch plane, its sweeps write the fluxes through the patch faces as
+// per patch plane (`faces`), its sweeps write the fluxes through the patch faces as
 // they compute them, and one launch at the end of a substep gathers the three
 // axes into the registers: a level step of 256^3 cells and 338 fine patches of
 // 40^3 stored cells (FP32) takes 2.54 ms, with three sweeps and three register
 // launches a substep 2.85.
 int level_sweeps(hydro_ctx* c, const hydro_ctx* coarse, const hydro_ctx* fine,
                  const hydro_amr_link* links, int32_t n, int g, bool fine_side, double dt,
-                 char* ws, const LevelLayout& lay, const AmrLink* dlinks) {
+                 char* ws, const LevelLayout& lay, bool faces, const AmrLink* dlinks) {
   static const int even[3] = {0, 1, 2}, odd[3] = {2, 1, 0};
   const int parity = int(c->step & 1);
   const int* order = parity ? odd : even;
@@ -2278,7 +2283,7 @@ int level_sweeps(hydro_ctx* c, const hydro_ctx* coarse, const hydro_ctx* fine,
     L.maxface = int32_t(lay.maxface);
     L.weight = dt;
   };
-  if (fine_side && c->cfg.batch_fuse && plane_ok(c, c->cfg)) {
+  if (fine_side && faces) {
     for (int i = 0; i < 2; ++i) {
       LaunchSweep S = (i == 0) == (parity == 0) ? plane_launch(c, parity == 0, i)
                                                 : sweep_launch(c, 2, i);
@@ -2347,13 +2352,11 @@ int hydro_amr_step(hydro_ctx* coarse, hydro_ctx* fine, const hydro_amr_link* lin
   if (rc) return rc;
   if (!(dt > 0.0) || !std::isfinite(dt)) return fail(HYDRO_EINVAL, "dt must be > 0 and finite");
   if (flags & ~uint32_t(HYDRO_AMR_NO_REFLUX)) return fail(HYDRO_EINVAL, "unknown flags");
-  size_t need = 0;
-  rc = hydro_amr_step_workspace_bytes(coarse, fine, fine_ng, &need);
-  if (rc) return rc;
-  if (!workspace || ws_bytes < need) return fail(HYDRO_EINVAL, "workspace too small");
-  if (reinterpret_cast<uintptr_t>(workspace) % 256) return fail(HYDRO_EINVAL, "workspace misaligned");
   const int g = fine_ng;
   const LevelLayout lay = level_layout(coarse, fine, g);  // n links, one per fine patch
+  if (!workspace || ws_bytes < lay.least) return fail(HYDRO_EINVAL, "workspace too small");
+  if (reinterpret_cast<uintptr_t>(workspace) % 256) return fail(HYDRO_EINVAL, "workspace misaligned");
+  const bool faces = level_fused(fine) && ws_bytes >= lay.total;
   char* ws = static_cast<char*>(workspace);
   void* cold = ws;
   double* reg = reinterpret_cast<double*>(ws + lay.reg);
@@ -2373,7 +2376,7 @@ int hydro_amr_step(hydro_ctx* coarse, hydro_ctx* fine, const hydro_amr_link* lin
   if (rc) return rc;
   HIP_TRY(hipMemsetAsync(reg, 0, size_t(2 * lay.nreg) * sizeof(double), st));
   // 1. the coarse step, registering its fluxes through the coarse-fine faces
-  rc = level_sweeps(coarse, coarse, fine, links, n, g, false, dt, ws, lay, dlinks);
+  rc = level_sweeps(coarse, coarse, fine, links, n, g, false, dt, ws, lay, faces, dlinks);
   if (rc) return rc;
   // 2. two fine substeps, ghosts from the coarse data interpolated in time
   for (int s = 0; s < 2; ++s) {
@@ -2387,7 +2390,7 @@ int hydro_amr_step(hydro_ctx* coarse, hydro_ctx* fine, const hydro_amr_link* lin
       }
     });
     if (rc) return rc;
-    rc = level_sweeps(fine, coarse, fine, links, n, g, true, 0.5 * dt, ws, lay, dlinks);
+    rc = level_sweeps(fine, coarse, fine, links, n, g, true, 0.5 * dt, ws, lay, faces, dlinks);
     if (rc) return rc;
   }
   // 3. restriction, 4. refluxing
