@@ -1872,6 +1872,13 @@ int hydro_diag_pdf(hydro_ctx* c, int quantity, double lo, double hi, int32_t nbi
   L.lo = lo;
   L.w = w;
   L.counts = reinterpret_cast<unsigned long long*>(counts);
+  auto count = [](const PatchDev& P) { return int64_t(P.n[0]) * P.n[1] * P.n[2]; };
+  if (c->batch) {
+    for (const PatchDev& P : c->patches) L.cells += count(P);
+    L.most = c->max_patch_cells;
+  } else {
+    L.cells = L.most = count(c->single);
+  }
   HIP_TRY(launch_diag_pdf(L, c->stream));
   return HYDRO_OK;
 }

@@ -93,7 +93,7 @@ struct DiagArgs {
   int nbins;
   double lo, w;
   unsigned long long* counts;
-  bool lds;                 // per-workgroup LDS counters (nbins + 2 <= kPdfLdsBins)
+  bool lds;                 // per-workgroup LDS counters (pdf_lds)
   int axis, chunks;
   FastDiv dnx, dny;         // single grid: division by nx and ny
   double rho_lo, drho, dx_axis;
@@ -111,7 +111,7 @@ struct DiagArgs {
 // density, 57 us so).  Up to 8192 counters take workgroups of 256 threads;
 // up to kPdfLdsBins, where one or two workgroups fill the LDS of a CU,
 // workgroups of 1024.  Counting straight into memory instead took 11.2 ms
-// for 20000 bins (0.10 ms so) and is left for more.
+// for 20000 bins (0.10 ms so) and is left for more, and for few cells (pdf_lds).
 template <class T, int Q, int BLOCK>
 __global__ void __launch_bounds__(BLOCK) pdf_kernel(DiagArgs<T> a) {
   extern __shared__ unsigned int hist[];
@@ -469,6 +469,22 @@ __global__ void __launch_bounds__(kDiagBlock) spectrum_final_kernel(const double
   }
 }
 
+// Whether a PDF counts in LDS: always up to kPdfNarrowBins counters, never above
+// kPdfLdsBins.  Between them a workgroup of 1024 threads clears and adds 9 to 40
+// counters a thread, which pays from 12 cells per counter on (grids, memory
+// against LDS: 64^3 cells and 39000 bins 17 against 20 us, 20000 bins 16.3 and
+// 16.4, 9000 bins 20 and 11; 16^3 and 39000 bins 9 and 14; batches: 64 patches of
+// 16^3 and 39000 bins 17 and 21, 9000 bins 20 and 11.5).  In a batch it also does
+// where one patch has a cell per counter, since four workgroups are all that a
+// patch has with counters in memory (one of 32^3 cells and 20000 bins 28 and 26,
+// 39000 bins 28 and 30).
+static bool pdf_lds(const LaunchDiag& L) {
+  const int64_t nb2 = int64_t(L.nbins) + 2;
+  if (nb2 <= kPdfNarrowBins) return true;
+  if (nb2 > kPdfLdsBins) return false;
+  return L.cells >= 12 * nb2 || (L.patches && L.most >= nb2);
+}
+
 template <class T>
 static DiagArgs<T> to_dargs(const LaunchDiag& L) {
   DiagArgs<T> a;
@@ -480,7 +496,7 @@ static DiagArgs<T> to_dargs(const LaunchDiag& L) {
   a.lo = L.lo;
   a.w = L.w;
   a.counts = L.counts;
-  a.lds = L.nbins + 2 <= kPdfLdsBins;
+  a.lds = pdf_lds(L);
   a.axis = L.axis;
   a.chunks = L.chunks;
   a.dnx = FastDiv(uint32_t(L.single.n[0]));
@@ -507,14 +523,18 @@ static hipError_t launch_pdf_t(const LaunchDiag& L, hipStream_t st) {
   if (L.patches) {
     grid = dim3(wide ? 1 : kPdfPatchBlocks, unsigned(L.npatch));
   } else {
-    // at least 8192 cells and 12 cells per counter to a workgroup (256^3
-    // cells: 16 bins 64 -> 45 us with half the workgroups of 4096 cells,
-    // 1000 bins 100 -> 55 us), one workgroup per CU of wide counters
-    const int64_t cells = int64_t(L.single.n[0]) * L.single.n[1] * L.single.n[2];
-    int64_t b = wide ? kPdfWideBlocks : std::min<int64_t>(cells / (12 * nb2), kPdfMaxBlocks);
-    b = std::max<int64_t>(std::min<int64_t>(b, cells / 8192), kPdfWideBlocks);
-    b = std::min<int64_t>(b, (cells + 4 * kDiagBlock - 1) / (4 * kDiagBlock));
-    grid = dim3(unsigned(std::max<int64_t>(1, a.lds ? b : kPdfMaxBlocks)));
+    // up to one workgroup for 8192 cells and for 12 cells per counter (256^3
+    // cells: 16 bins 64 -> 45 us with half the workgroups of 4096 cells, 1000
+    // bins 100 -> 55 us), or one per CU if that is more (256 of them; all of
+    // the wide counters').  In any case 1024 cells to a workgroup, the only
+    // bound with counters in memory
+    int64_t b = kPdfMaxBlocks;
+    if (wide)
+      b = kPdfWideBlocks;
+    else if (a.lds)
+      b = std::max<int64_t>(std::min(L.cells / (12 * nb2), L.cells / 8192), kPdfWideBlocks);
+    b = std::min<int64_t>({b, kPdfMaxBlocks, (L.cells + 4 * kDiagBlock - 1) / (4 * kDiagBlock)});
+    grid = dim3(unsigned(std::max<int64_t>(1, b)));
   }
   auto run = [&](auto narrow_kernel, auto wide_kernel) {
     if (wide)

@@ -123,6 +123,7 @@ struct LaunchDiag {
   int32_t nbins;
   double lo, w;                   // w = nbins / (hi - lo)
   unsigned long long* counts;     // device, nbins + 2
+  int64_t cells, most;            // interior cells in all, and of the largest patch
   // slab profiles (single grid)
   int32_t axis;
   int32_t chunks;                 // partial sums per slab
