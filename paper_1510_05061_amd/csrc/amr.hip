@@ -64,7 +64,6 @@ struct AmrArgs {
   int ng;                   // single grid: stored ghost layers
   int bc[6];
   AmrLink links[kAmrLinksPerLaunch];
-  int ghosts_only;
   T* fpool;                 // fine side of the links
   const PatchDev* fpatches;
   int finset;
@@ -273,10 +272,10 @@ __device__ __forceinline__ void link_block(int& link, unsigned& bx) {
   }
 }
 
-// Fine cells (interior, or the stored ghost shell) of a link, one coarse
-// parent per thread: per variable the parent's value and its three limited
-// slopes are formed once and give its children, written as x pairs (PAIR:
-// one access each).  Fine extents are even, so a parent's children are all
+// Fine cells (interior, or with SHELL the stored ghost shell) of a link, one
+// coarse parent per thread, of variable blockIdx.z (SHELL) or of all five: per
+// variable the parent's value and its three limited slopes are formed once and
+// give its children, written as x pairs (PAIR: one access each).  Fine extents are even, so a parent's children are all
 // inside or all outside the interior, and only with an odd number of ghost
 // layers (ODD) can some of them lie beyond the stored shell.
 //
@@ -291,17 +290,21 @@ __device__ __forceinline__ void link_block(int& link, unsigned& bx) {
 // of parents (2047 instructions a thread, now about 850): 128 FP32 links of
 // 32^3 cells, interior 51 -> 31 us, 4 ghost layers 137 -> 104 us; the level
 // step's 338 shells of 4 layers 209 -> 167 us, interpolated 272 -> 245 us.
-template <class T, bool COLD, bool PAIR, bool ODD>
+//
+// A shell has few parents; with a variable to a thread it has five times the
+// waves, each of fewer registers.  FP32 links of 64^3 cells, 2 layers: one link
+// 7.9 -> 4.6 us, 16 22.4 -> 14.5, 64 87 -> 76 (4 layers 111 -> 102).  The interior
+// of 64 links takes 155 us with all five, 163 with one.
+template <class T, bool COLD, bool PAIR, bool ODD, bool SHELL>
 __device__ void prolong_link(const AmrArgs<T>& a, const AmrLink& L, const PatchDev& F,
                              const PatchDev& C, unsigned bx) {
-  const bool shell = a.ghosts_only != 0;  // without stored ghosts: no cells
-  const int g = shell ? F.ng : 0;
+  const int g = SHELL ? F.ng : 0;  // a shell without stored ghosts has no cells
   const int h = (g + 1) >> 1;  // parents beyond the interior's on each side
   const unsigned ix = unsigned(F.n[0]) >> 1, iy = unsigned(F.n[1]) >> 1,
                  iz = unsigned(F.n[2]) >> 1;  // the interior's parents
   const unsigned o = 2u * unsigned(h), px = ix + o, py = iy + o;
   const unsigned zpart = o * py * px, ypart = iz * o * px;
-  const unsigned total = shell ? zpart + ypart + iz * iy * o : iz * iy * ix;
+  const unsigned total = SHELL ? zpart + ypart + iz * iy * o : iz * iy * ix;
   // t-th parent outside [0, I) along an axis: -h .. -1, then I ..
   auto outside = [&](unsigned t, unsigned I) {
     return int(t) < h ? int(t) - h : int(I) + int(t) - h;
@@ -324,7 +327,7 @@ __device__ void prolong_link(const AmrArgs<T>& a, const AmrLink& L, const PatchD
   const double th = a.theta;
   for (unsigned c = bx * kAmrBlock + threadIdx.x; c < total; c += gridDim.x * kAmrBlock) {
     int pi, pj, pk;
-    if (!shell) {
+    if (!SHELL) {
       const unsigned row = c / ix, kk = row / iy;
       pi = int(c - row * ix);
       pj = int(row - kk * iy);
@@ -349,11 +352,13 @@ __device__ void prolong_link(const AmrArgs<T>& a, const AmrLink& L, const PatchD
                         unsigned(pk + h + 1) * csz;
     const unsigned fc = unsigned(2 * pi + g) * unsigned(sizeof(T)) + unsigned(2 * pj + g) * fsy +
                         unsigned(2 * pk + g) * fsz;
-    double u[5][7];
+    constexpr int NV = SHELL ? 1 : 5;  // variables v0 .. v0 + NV - 1
+    const int v0 = SHELL ? int(blockIdx.z) : 0;
+    double u[NV][7];
 #pragma unroll
-    for (int v = 0; v < 5; ++v) {
-      const T* q = c0 + v * C.plane;
-      const T* qo = COLD ? o0 + v * C.plane : nullptr;
+    for (int v = 0; v < NV; ++v) {
+      const T* q = c0 + (v0 + v) * C.plane;
+      const T* qo = COLD ? o0 + (v0 + v) * C.plane : nullptr;
       // coarse value at byte offset b, interpolated in time when a start copy is given
       auto cv = [&](unsigned b) {
         if constexpr (!COLD) {
@@ -372,12 +377,12 @@ __device__ void prolong_link(const AmrArgs<T>& a, const AmrLink& L, const PatchD
       u[v][6] = cv(pc + csz);
     }
 #pragma unroll
-    for (int v = 0; v < 5; ++v) {
+    for (int v = 0; v < NV; ++v) {
       const double w = u[v][0];
       const double dx = mc_slope(w - u[v][1], u[v][2] - w);
       const double dy = mc_slope(w - u[v][3], u[v][4] - w);
       const double dz = mc_slope(w - u[v][5], u[v][6] - w);
-      T* fv = f0 + v * F.plane;
+      T* fv = f0 + (v0 + v) * F.plane;
       const double x0 = w + -0.25 * dx, x1 = w + 0.25 * dx;
 #pragma unroll
       for (int r = 0; r < 4; ++r) {
@@ -398,19 +403,19 @@ __device__ void prolong_link(const AmrArgs<T>& a, const AmrLink& L, const PatchD
   }
 }
 
-template <class T, bool COLD>
+template <class T, bool COLD, bool SHELL>
 __global__ void __launch_bounds__(kAmrBlock) prolong_kernel(AmrArgs<T> a) {
   int l;
   unsigned bx;
   link_block(l, bx);
   const AmrLink L = link_of(a, l);
   const PatchDev F = fine_patch(a.fpatches, L.fine, a.finset), C = a.patches[L.coarse];
-  if (a.ghosts_only && (F.ng & 1))
-    prolong_link<T, COLD, false, true>(a, L, F, C, bx);
+  if (SHELL && (F.ng & 1))
+    prolong_link<T, COLD, false, SHELL, SHELL>(a, L, F, C, bx);
   else if (pairs_aligned(F))
-    prolong_link<T, COLD, true, false>(a, L, F, C, bx);
+    prolong_link<T, COLD, true, false, SHELL>(a, L, F, C, bx);
   else
-    prolong_link<T, COLD, false, false>(a, L, F, C, bx);
+    prolong_link<T, COLD, false, false, SHELL>(a, L, F, C, bx);
 }
 
 // Copy of the coarse cells within a.margin of the box link blockIdx.y
@@ -678,7 +683,6 @@ static AmrArgs<T> to_aargs(const LaunchAmr& L) {
     const int m = std::min<int32_t>(L.nlinks, kAmrLinksPerLaunch);
     for (int i = 0; i < m; ++i) a.links[i] = L.links[i];
   }
-  a.ghosts_only = L.ghosts_only;
   a.fpool = L.fpool ? static_cast<T*>(L.fpool) : a.pool;
   a.fpatches = L.fpatches ? L.fpatches : L.patches;
   a.finset = L.finset;
@@ -743,11 +747,13 @@ static hipError_t launch_amr_t(const LaunchAmr& L, hipStream_t st) {
     hipLaunchKernelGGL(restrict_kernel<T>, dim3(amr_blocks(L.cells), unsigned(L.nlinks)),
                        dim3(kAmrBlock), 0, st, a);
   } else if (L.op == kAmrProlong) {
-    const dim3 grid(amr_blocks(L.cells), unsigned(L.nlinks));
-    if (L.cold)
-      hipLaunchKernelGGL((prolong_kernel<T, true>), grid, dim3(kAmrBlock), 0, st, a);
+    const dim3 grid(amr_blocks(L.cells), unsigned(L.nlinks), L.ghosts_only ? 5u : 1u);
+    if (!L.ghosts_only)
+      hipLaunchKernelGGL((prolong_kernel<T, false, false>), grid, dim3(kAmrBlock), 0, st, a);
+    else if (L.cold)
+      hipLaunchKernelGGL((prolong_kernel<T, true, true>), grid, dim3(kAmrBlock), 0, st, a);
     else
-      hipLaunchKernelGGL((prolong_kernel<T, false>), grid, dim3(kAmrBlock), 0, st, a);
+      hipLaunchKernelGGL((prolong_kernel<T, false, true>), grid, dim3(kAmrBlock), 0, st, a);
   } else if (L.op == kAmrSnapshot) {
     hipLaunchKernelGGL(snapshot_kernel<T>, dim3(amr_blocks(L.cells), unsigned(L.nlinks)),
                        dim3(kAmrBlock), 0, st, a);
@@ -767,6 +773,7 @@ static hipError_t launch_amr_t(const LaunchAmr& L, hipStream_t st) {
 hipError_t launch_amr(const LaunchAmr& L, hipStream_t st) {
   if (L.op < kAmrFill || L.op > kAmrGather) return hipErrorInvalidValue;
   if (L.op == kAmrSnapshot && (!L.cold || L.margin < 0)) return hipErrorInvalidValue;
+  if (L.op == kAmrProlong && L.cold && !L.ghosts_only) return hipErrorInvalidValue;
   if (L.op != kAmrFill &&
       (!L.patches || L.nlinks < 1 || (!L.dlinks && L.nlinks > kAmrLinksPerLaunch) ||
        L.nlinks > 65535))
