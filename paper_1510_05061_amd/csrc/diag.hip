@@ -267,12 +267,14 @@ __global__ void __launch_bounds__(kXslabBlock) profile_xslab_kernel(DiagArgs<T> 
 #pragma unroll
   for (int v = 0; v < 5; ++v) red[v][threadIdx.x] = acc[v];
   __syncthreads();
-  // sum i = (x, v) of the tile
+  // sum i = (x, v) of the tile, over the row groups that had a row (the others
+  // hold zeros: a grid of 2 x 1 x 1 cells has one of 512)
+  const int used = max(1, min(R, int(rows) - c * R));
   for (int i = threadIdx.x; i < 5 * w; i += kXslabBlock) {
     const int xo = i / 5, v = i - 5 * xo, xg = blockIdx.y * w + xo;
     if (xg >= P.n[0]) continue;
     double t = red[v][xo];
-    for (int q = 1; q < R; ++q) t += red[v][q * w + xo];
+    for (int q = 1; q < used; ++q) t += red[v][q * w + xo];
     a.partials[(int64_t(xg) * a.chunks + c) * 5 + v] = t;
   }
 }
