@@ -500,10 +500,9 @@ LaunchReduce reduce_launch(const hydro_ctx* c) {
   L.patches = c->batch ? c->d_patches : nullptr;
   L.single = c->single;
   L.npatch = c->batch ? c->npatch : 1;
-  L.chunks = c->batch ? kBatchChunks
-                      : chunks_for(int64_t(c->single.n[0]) * c->single.n[1] * c->single.n[2]);
-  L.cfl_chunks = c->batch ? cfl_chunks(c->max_patch_cells, c->npatch)
-                          : cfl_chunks(int64_t(c->single.n[0]) * c->single.n[1] * c->single.n[2], 1);
+  L.cells = c->batch ? c->max_patch_cells : int64_t(c->single.n[0]) * c->single.n[1] * c->single.n[2];
+  L.chunks = c->batch ? kBatchChunks : chunks_for(L.cells);
+  L.cfl_chunks = cfl_chunks(L.cells, L.npatch);
   L.gamma = c->desc.gamma;
   for (int a = 0; a < 3; ++a) L.grav[a] = c->desc.grav[a];
   L.scal = c->scal;

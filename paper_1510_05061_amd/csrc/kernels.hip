@@ -2065,10 +2065,13 @@ struct ReduceArgs {
 // workgroups per patch whatever its size) a batch of one 256^3 FP32 patch
 // took 11.56 ms; with workgroups by size it takes 0.08 ms
 // (4.2 TB/s); a 256^3 FP32 grid 0.090 -> 0.081 ms, host wait included.
-template <class T>
+// U = 4; from kCflLarge cells on 2, where more waves stream better than more
+// loads a wave (512^3 with the wait: FP32 541 -> 481 us, FP64 931 -> 915; 128^3
+// FP64 42.7 with four, 46.3 with two).
+constexpr int64_t kCflLarge = int64_t(1) << 24;
+template <class T, unsigned U>
 __global__ void __launch_bounds__(256) cfl_kernel(ReduceArgs<T> a) {
   __shared__ T red[16];
-  constexpr unsigned U = 4;
   const PatchDev P = a.patches ? a.patches[blockIdx.y] : a.single;
   const unsigned nx = unsigned(P.n[0]), ny = unsigned(P.n[1]);
   const unsigned cells = nx * ny * unsigned(P.n[2]);  // a plane is below 4 GiB
@@ -2592,10 +2595,13 @@ static ReduceArgs<T> to_rargs(const LaunchReduce& L) {
 // L.fold_only (a step without sweeps: its bookkeeping takes the maximum).
 hipError_t launch_cfl(const LaunchReduce& L, hipStream_t st) {
   dim3 grid(L.cfl_chunks, L.npatch);
+  const bool large = L.cells >= kCflLarge;
   if (L.fp64)
-    hipLaunchKernelGGL(cfl_kernel<double>, grid, dim3(256), 0, st, to_rargs<double>(L));
+    hipLaunchKernelGGL((large ? cfl_kernel<double, 2> : cfl_kernel<double, 4>), grid, dim3(256), 0,
+                       st, to_rargs<double>(L));
   else
-    hipLaunchKernelGGL(cfl_kernel<float>, grid, dim3(256), 0, st, to_rargs<float>(L));
+    hipLaunchKernelGGL((large ? cfl_kernel<float, 2> : cfl_kernel<float, 4>), grid, dim3(256), 0,
+                       st, to_rargs<float>(L));
   hipError_t e = hipGetLastError();
   if (e != hipSuccess || L.psmax || L.fold_only) return e;
   hipLaunchKernelGGL(finish_cfl_kernel, dim3(1), dim3(1), 0, st, L.scal);

@@ -89,6 +89,7 @@ struct LaunchReduce {
   int32_t npatch;
   int32_t chunks;      // totals: workgroups (partial sums) per patch
   int32_t cfl_chunks;  // CFL: workgroups per patch
+  int64_t cells;       // CFL: cells of the largest patch
   double gamma;
   double grav[3];
   DevScalars* scal;
