@@ -2065,9 +2065,10 @@ struct ReduceArgs {
 // workgroups per patch whatever its size) a batch of one 256^3 FP32 patch
 // took 11.56 ms; with workgroups by size it takes 0.08 ms
 // (4.2 TB/s); a 256^3 FP32 grid 0.090 -> 0.081 ms, host wait included.
-// U = 4; from kCflLarge cells on 2, where more waves stream better than more
-// loads a wave (512^3 with the wait: FP32 541 -> 481 us, FP64 931 -> 915; 128^3
-// FP64 42.7 with four, 46.3 with two).
+// U = 4; for one grid or patch of kCflLarge cells and more 2, which streams
+// better (512^3 with the wait: FP32 541 -> 481 us, FP64 931 -> 915; 128^3 FP64 42.7
+// with four, 46.3 with two).  A large patch among many has few workgroups and
+// needs its loads in flight (256^3 beside 1000 of 16^3 4.4 ms, with two 13.1).
 constexpr int64_t kCflLarge = int64_t(1) << 24;
 template <class T, unsigned U>
 __global__ void __launch_bounds__(256) cfl_kernel(ReduceArgs<T> a) {
@@ -2595,7 +2596,7 @@ static ReduceArgs<T> to_rargs(const LaunchReduce& L) {
 // L.fold_only (a step without sweeps: its bookkeeping takes the maximum).
 hipError_t launch_cfl(const LaunchReduce& L, hipStream_t st) {
   dim3 grid(L.cfl_chunks, L.npatch);
-  const bool large = L.cells >= kCflLarge;
+  const bool large = L.cells >= kCflLarge && L.npatch == 1;
   if (L.fp64)
     hipLaunchKernelGGL((large ? cfl_kernel<double, 2> : cfl_kernel<double, 4>), grid, dim3(256), 0,
                        st, to_rargs<double>(L));
