@@ -452,7 +452,8 @@ __global__ void __launch_bounds__(kSpecBlock, 2)
   for (int k = threadIdx.x; k < nk; k += kSpecBlock) {
     const int km = k == 0 ? 0 : n - k;
     double s = 0.0;
-    for (int h = 0; h < ng; ++h) s += pw[h * n + k] + pw[h * n + km];
+    // (groups past the lines of a pass hold zeros)
+    for (int h = 0; h < min(ng, nl); ++h) s += pw[h * n + k] + pw[h * n + km];
     a.partials[int64_t(blockIdx.x) * nk + k] = 0.5 * s;
   }
 }
