@@ -281,14 +281,13 @@ __global__ void __launch_bounds__(kXslabBlock) profile_xslab_kernel(DiagArgs<T> 
 
 // Sum of v over the workgroup in a fixed order (wave shuffles, then the
 // waves in order); the result is returned to every thread.
-template <int BLOCK = kDiagBlock>
 __device__ __forceinline__ double block_sum(double v, double* red) {
   for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off);
   __syncthreads();  // red is free
   if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = v;
   __syncthreads();
   double t = red[0];
-  for (int w = 1; w < BLOCK / 64; ++w) t += red[w];
+  for (int w = 1; w < kDiagBlock / 64; ++w) t += red[w];
   return t;
 }
 
@@ -301,7 +300,8 @@ __global__ void __launch_bounds__(kFinalBlock) profile_final_kernel(const double
                                                                      int nslab, int chunks,
                                                                      double cells_per_slab,
                                                                      double dx_axis, double* out) {
-  __shared__ double red[kFinalBlock / 64];
+  constexpr int NW = kFinalBlock / 64;
+  __shared__ double red[3][NW];
   double w = 0.0, num = 0.0, den = 0.0;
   // the means: a thread per slab and field, eight partials in flight
   for (int i = threadIdx.x; i < 5 * nslab; i += kFinalBlock) {
@@ -326,10 +326,27 @@ __global__ void __launch_bounds__(kFinalBlock) profile_final_kernel(const double
     den += f * (1.0 - f);
     num += out[s * 5 + 4];
   }
-  w = block_sum<kFinalBlock>(w, red);
-  den = block_sum<kFinalBlock>(den, red);
-  num = block_sum<kFinalBlock>(num, red);
+  // the three sums together: wave shuffles, then the waves in order
+  for (int off = 32; off > 0; off >>= 1) {
+    w += __shfl_xor(w, off);
+    den += __shfl_xor(den, off);
+    num += __shfl_xor(num, off);
+  }
+  if ((threadIdx.x & 63) == 0) {
+    red[0][threadIdx.x >> 6] = w;
+    red[1][threadIdx.x >> 6] = den;
+    red[2][threadIdx.x >> 6] = num;
+  }
+  __syncthreads();
   if (threadIdx.x == 0) {
+    w = red[0][0];
+    den = red[1][0];
+    num = red[2][0];
+    for (int q = 1; q < NW; ++q) {
+      w += red[0][q];
+      den += red[1][q];
+      num += red[2][q];
+    }
     out[nslab * 5] = w * dx_axis;
     out[nslab * 5 + 1] = den > 0.0 ? num / den : 0.0;
   }
