@@ -2380,7 +2380,8 @@ int hydro_amr_step(hydro_ctx* coarse, hydro_ctx* fine, const hydro_amr_link* lin
     L.margin = (g + 1) / 2 + 1;
   });
   if (rc) return rc;
-  HIP_TRY(hipMemsetAsync(reg, 0, size_t(2 * lay.nreg) * sizeof(double), st));
+  // a fill kernel: a memset node of a captured step was replayed wrongly
+  HIP_TRY(launch_fill(reg, 2 * lay.nreg, 0.0, st));
   // 1. the coarse step, registering its fluxes through the coarse-fine faces
   rc = level_sweeps(coarse, coarse, fine, links, n, g, false, dt, ws, lay, faces, dlinks);
   if (rc) return rc;
