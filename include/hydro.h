@@ -357,10 +357,10 @@ int hydro_diag_spectrum(hydro_ctx* c, double* out);
  * (256-byte aligned) of the bytes that hydro_diag_spectrum3d_workspace_bytes
  * reports: the three half spectra, their power and the partial spectra, about
  * 28 bytes per cell, with rows of nx / 2 + 1 values padded to multiples of 8
- * where nx >= 128.  A buffer without room for that padding is taken too (the
- * same bits, slower); a smaller one is HYDRO_EINVAL.  Its contents are
- * overwritten and need not be kept between calls.  Sums run in a fixed order: bitwise reproducible for a
- * shape.  Asynchronous on the context's stream (the state and `work` must
+ * where that takes at most an eighth more.  A buffer without room for that
+ * padding is taken too (the same bits, slower); a smaller one is HYDRO_EINVAL.
+ * Its contents are overwritten and need not be kept between calls.  Sums run in
+ * a fixed order: bitwise reproducible for a shape.  Asynchronous on the context's stream (the state and `work` must
  * stay valid until it completes).  Errors: HYDRO_EINVAL, HYDRO_ESTATE
  * (batch context), HYDRO_EDEVICE. */
 int hydro_diag_spectrum3d_workspace_bytes(hydro_ctx* c, size_t* bytes, int32_t* nshells);

@@ -45,13 +45,12 @@ template <class T>
 constexpr int kS3Elems = sizeof(T) == 8 ? 3072 : 4096;
 constexpr int kS3MaxLen = 1024;
 constexpr int kS3ColElems = 4096;  // complex elements of a y or z tile, at most
-// Lines of kS3PitchLen cells and up: kx rows start on multiples of kS3Pitch
-// complex values (128 bytes), at most a ninth more memory.  On shorter ones the
-// padding would be up to four times the rows, and rows lie back to back, as
-// they do in a workspace too small for the padding: 16 x 512^2 FP32 cells
-// (padded) 280 -> 241 us, 64 x 512^2 665 -> 623, 96 x 512^2 919 -> 883,
-// 96 x 384^2 594 -> 611.
-constexpr int kS3Pitch = 8, kS3PitchLen = 128;
+// kx rows start on multiples of kS3Pitch complex values (128 bytes) where that
+// takes at most an eighth more memory, which is all lines from 128 cells on.
+// Else (up to four times, lines of two cells) rows lie back to back, as they do
+// in a workspace too small for the padding: 16 x 512^2 FP32 cells (padded)
+// 280 -> 241 us, 64 x 512^2 665 -> 623, 96 x 512^2 919 -> 883, 96 x 384^2 594 -> 611.
+constexpr int kS3Pitch = 8;
 
 // kx columns per tile of a y or z pass over lines of length n: 8, whole
 // 128-byte lines of a row (the z pass strides by a plane: with half lines it
@@ -338,8 +337,8 @@ __global__ void __launch_bounds__(kS3Block) spec3_final_kernel(const double* par
 // Row pitch of the half spectra of lines of nx cells: the preferred one, and
 // the least.
 static int s3_pitch(int nx) {
-  const int nh = nx / 2 + 1;
-  return nx >= kS3PitchLen ? (nh + kS3Pitch - 1) / kS3Pitch * kS3Pitch : nh;
+  const int nh = nx / 2 + 1, np = (nh + kS3Pitch - 1) / kS3Pitch * kS3Pitch;
+  return 8 * np <= 9 * nh ? np : nh;
 }
 static int s3_pitch_least(int nx) { return nx / 2 + 1; }
 
