@@ -112,22 +112,31 @@ __global__ void __launch_bounds__(kBurnBlock) burn_kernel(BurnArgs<T> a) {
   const double temp = ((a.gamma - 1.0) * (e - (0.5 * m2) / r)) / r;
   // Ta / T for every link from one reciprocal: the residual of the product
   // corrects it to the quotient (a rounding error of the exponent would be
-  // carried through all substeps).  Where the product or 1 / T overflows, or T
-  // is no finite number, the correction is NaN and the quotient is divided out.
+  // carried through all substeps).  Where a product or 1 / T overflows, or T is
+  // no finite number, the correction is NaN and the quotients are divided out,
+  // behind one branch (with one a link the exponentials no longer overlap:
+  // 19 species, 18 substeps on 72 x 114 x 31 zones 18.3 instead of 16.6 us).
   const double itemp = 1.0 / temp;
-  auto over_temp = [&](double ta) {
-    const double q = ta * itemp, c = fma(fma(-q, temp, ta), itemp, q);
-    return __builtin_expect(c == c, 1) ? c : ta / temp;
-  };
+  bool exact = true;
+#pragma unroll
+  for (int s = 0; s < M - 1; ++s) {
+    const double q = a.Ta[s] * itemp;
+    d[s] = fma(fma(-q, temp, a.Ta[s]), itemp, q);
+    exact = exact && d[s] == d[s];
+  }
+  if (__builtin_expect(!exact, 0)) {
+#pragma unroll
+    for (int s = 0; s < M - 1; ++s) d[s] = a.Ta[s] / temp;
+  }
   double e0 = 0.0;
 #pragma unroll
   for (int s = 0; s < M; ++s) e0 += a.B[s] * X[s];
   c[0] = 0.0;
+  d[M - 1] = 1.0;
 #pragma unroll
-  for (int s = 0; s < M; ++s) {
-    const double hk = s < M - 1 ? a.h * (a.A[s] * exp(-over_temp(a.Ta[s]))) : 0.0;
-    d[s] = s < M - 1 ? recip(1.0 + hk) : 1.0;
-    if (s + 1 < M) c[s + 1] = hk;
+  for (int s = 0; s < M - 1; ++s) {
+    c[s + 1] = a.h * (a.A[s] * exp(-d[s]));
+    d[s] = recip(1.0 + c[s + 1]);
   }
   bool scaled = a.nsub >= kScaledSubsteps;
   if (scaled) {
