@@ -72,11 +72,12 @@ __device__ __forceinline__ void all_substeps(int nsub, First first, Next next) {
 // W_s = X_s / a_s with a_s = e_1 .. e_s, e_s = c_s d_s: the update
 // X_s <- d_s X_s + e_s X_{s-1} becomes W_s <- d_s W_s + W_{s-1}, one FMA (and
 // one rounding) per species and substep instead of two.  The scaling costs
-// about 14 instructions per species, two an update are saved: it pays from
-// seven substeps on.  A zone whose a_s leave [2^-400, 2^64] (a frozen link) or,
+// about 14 instructions per species and saves one an update.  192^3 FP32 zones,
+// 13 species, scaled and plain: 8 substeps 225 and 217 us, 12 236 and 236, 16
+// 247 and 262 (20 species 347 and 337, 363 and 370, 388 and 398).  A zone whose a_s leave [2^-400, 2^64] (a frozen link) or,
 // in FP64, with a species above 2^600 is stepped as it stands: the bounds keep W
 // within range and X / a_s from underflow.
-constexpr int kScaledSubsteps = 8;
+constexpr int kScaledSubsteps = 12;
 
 // 1 / x: the estimate after two Newton steps whose residuals are exact is
 // rounded as the quotient is, in half the instructions of a division (the same
@@ -86,7 +87,9 @@ __device__ __forceinline__ double recip(double x) {
   return __builtin_amdgcn_div_fixup(rcp(x), x, 1.0);
 }
 
-// The kernel is bound by FP64 issue.  13 species and 64 substeps on 256^3
+// The kernel is bound by FP64 issue: 1563 VALU instructions a zone with 13
+// species and 64 substeps (832 the substeps), 92 % of the cycles that a SIMD is
+// busy, at a clock that falls to 1.9 GHz.  13 species and 64 substeps on 256^3
 // FP32 zones: with (X_s + c_s X_{s-1}) d_s as three operations, a division
 // per link for Ta / T and the network's constants hoisted out of a
 // grid-stride loop into spilled scalars 1.72 ms; with divisions 1 / (1 + h k)
