@@ -797,6 +797,16 @@ def kernel_source_hash():
     return h.hexdigest()[:16]
 
 
+def library_source_hash():
+    """Hash of every source of the library (named by the kernel traces of
+    the operators, which kernel_source_hash does not cover)."""
+    h = hashlib.sha256()
+    csrc = os.path.join(ROOT, "paper_1510_05061_amd", "csrc")
+    for f in sorted(os.listdir(csrc)):
+        h.update(open(os.path.join(csrc, f), "rb").read())
+    return h.hexdigest()[:16]
+
+
 def counter_entry(workload, kernel, precision):
     """The committed counter summary's entry for `kernel`, or None when it is
     missing or was taken on different kernel source."""
@@ -932,6 +942,7 @@ def main():
         "copy_ceiling": copy_ceiling(torch, bytes32),
         "stream_ceiling": stream32,
         "kernel_source": kernel_source_hash(),
+        "library_source": library_source_hash(),
         "diagnostics": diag32,
     }
     if W["kind"] == "batch" and not args.skip_loop:

@@ -435,7 +435,7 @@ int hydro_amr_restrict(hydro_ctx* c, const hydro_amr_link* links, int32_t n);
  * D = sign(a) min(2|a|, 2|b|, |a+b|/2) when the coarse one-sided
  * differences a, b have a positive product, else 0.  ghosts_only = 0 fills
  * the fine interior; 1 fills only the fine ghost shell (coarse-fine ghost
- * exchange).  The coarse cells used (parents and their neighbours, coarse
+ * exchange; a fine patch that stores no ghosts is left as it is).  The coarse cells used (parents and their neighbours, coarse
  * ghosts included: fill them first) must lie in the coarse patch's stored
  * region.  Same independence rule and errors as hydro_amr_restrict. */
 int hydro_amr_prolong(hydro_ctx* c, const hydro_amr_link* links, int32_t n, int ghosts_only);

@@ -126,9 +126,10 @@ __device__ __forceinline__ int t2_of(int axis) { return axis == 2 ? 1 : 2; }
 // stores) at 32-bit offsets from the stored corner.
 //
 // What bounds the fill are the row ends: runs of g cells, often in lines of
-// their own, where memory writes a part of a 64-byte sector at the cost of
-// reading it first (a strided write of 16 or 32 bytes takes 2.3 times one of
-// 64).  The stores go past the caches: nothing here reads them again.
+// their own, written in parts of a 64-byte sector.  Such writes of 16 or 32
+// bytes take 2.6 to 3.9 times those of a whole sector, about 0.044 ns each over
+// the chip; the fill below of padded rows makes 7.4e7 of them (3.2 of its
+// 5.2 ms), 3.0e7 of whole sectors (0.5 ms) and reads 8.1 GB.  The stores go past the caches: nothing here reads them again.
 // 1024 64^3 and 1024 32^3 patches, against a walk over every stored cell
 // with plain stores and 64-bit offsets: 4 FP32 layers, rows back to back
 // 3.44 -> 2.07 ms, padded to 128-byte lines 5.1 -> 5.2 ms (4.7 to 5.4 with
@@ -289,7 +290,8 @@ __device__ __forceinline__ void link_block(int& link, unsigned& bx) {
 // fill).  Against one test and one 64-bit offset per child over the whole box
 // of parents (2047 instructions a thread, now about 850): 128 FP32 links of
 // 32^3 cells, interior 51 -> 31 us, 4 ghost layers 137 -> 104 us; the level
-// step's 338 shells of 4 layers 209 -> 167 us, interpolated 272 -> 245 us.
+// step's 338 shells of 4 layers 209 -> 167 us, interpolated 272 -> 245 us (now, a
+// variable to a thread, 146 and 175).
 //
 // A shell has few parents; with a variable to a thread it has five times the
 // waves, each of fewer registers.  FP32 links of 64^3 cells, 2 layers: one link
