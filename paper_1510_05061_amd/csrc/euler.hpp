@@ -229,7 +229,9 @@ __device__ __forceinline__ void face_states(const Prim<T>& Wl, const Prim<T>& W,
 // p + S_K g a, and one reciprocal serves the whole correction.
 // Every term carries g, so a state with S* = u (a contact at rest, a mirror
 // wall) gets no correction at all, whatever the rounding of the reciprocal;
-// off the star region g S_K is set to zero instead of branching.
+// off the star region g S_K is set to zero instead of branching, and with it a
+// and S*: they may be infinite or NaN there (both sound speeds are NaN where
+// both sides have lost their pressure), and F_K must not see them.
 // The sweeps that hold planes in LDS are bound by instruction issue: written
 // term by term (with p/(S_K - u) and two more products per variable) the
 // column march had 2962 VALU instructions instead of 2789, and a step pair
@@ -257,6 +259,7 @@ __device__ __forceinline__ Cons<T> hllc(const Prim<T>& L, const Prim<T>& R,
   T p = left ? L.p : R.p;
   T S = left ? SL : SR;
   T a = left ? aL : aR;
+  a = star ? a : T(0);
   T v2 = fma_(u, u, fma_(t1, t1, t2 * t2));
   T H = fma_(p, k.enthalpy, T(0.5) * r * v2);  // E + p
   T sg = S * div_(Ss - u, S - Ss);
@@ -266,7 +269,7 @@ __device__ __forceinline__ Cons<T> hllc(const Prim<T>& L, const Prim<T>& R,
   F.mn = fma_(F.r, u, fma_(sg, a, p));
   F.mt1 = F.r * t1;
   F.mt2 = F.r * t2;
-  F.e = fma_(sg, fma_(a, Ss, H), u * H);
+  F.e = fma_(sg, fma_(a, star ? Ss : T(0), H), u * H);
   return F;
 }
 
